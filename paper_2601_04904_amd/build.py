@@ -19,6 +19,9 @@ FLAGS = [
     "-O3", "-std=c++20", "-fPIC", "-shared", "--offload-arch=gfx950",
     # no packed FP32 instructions in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # MFMA accumulators in plain VGPRs: left to itself the compiler moves them to the
+    # accumulator half of the register file and copies them in and out around the loop
+    "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-Wno-unused-result",
     "-I", os.path.join(ROOT, "include"),
 ]

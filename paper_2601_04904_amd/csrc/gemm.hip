@@ -5,21 +5,32 @@
 // launch executes a list of independent products, each tiled into 64 x 32
 // complex output tiles; a workgroup owns one tile of one product.
 //
-// Complex arithmetic on real MFMA: a complex m x k matrix A stored as
-// interleaved (re, im) doubles is read as the real m x 2k matrix A', and
-// op(B) (k x n complex) is expanded on the fly into the real 2k x 2n matrix
+// FP64 path: v_mfma_f64_16x16x4 on the real and imaginary parts, four MFMAs per
+// 16 x 16 x 4 complex block (an element is one 16-byte (re, im) pair in memory,
+// LDS and registers, so both parts come with one read).
+//
+// What bounds it: the FP64 matrix rate (77.5 TFLOP/s measured with operands in
+// registers).  On 32 products of 512 x 512 with distinct random operands the
+// 64 x 64 tile runs at 69.6 TFLOP/s (493 us), on 16 of 1024 at 71.5; with the
+// 4x4x4 instruction, A replicated over its blocks, and the memory instructions
+// of a stage issued in blocks of their own it was 51 to 60 (two 256-thread
+// workgroups per CU).  The accumulators must stay in plain VGPRs: in the
+// accumulator half of the register file the compiler copies them in and out
+// around every stage, which halves the rate of the 16x16x4 instruction (36
+// against 77.5 TFLOP/s in a loop of it alone).
+//
+// Mixed path: complex arithmetic on real MFMA by a 2 x 2 real embedding.  A
+// complex m x k matrix A stored as interleaved (re, im) is read as the real
+// m x 2k matrix A', and op(B) (k x n complex) is expanded on the fly into the
+// real 2k x 2n matrix
 //     B''[2p+c][2j+d] = Re B[p][j]  (c == d),  Im B[p][j] (c=0,d=1),
 //                       -Im B[p][j] (c=1,d=0)
-// so that A' B'' is the interleaved complex product.  The real product has
-// 4mnk multiply-adds, the same as four planar real products, and both the
-// A operand and the output keep the interleaved storage.
-//
-// FP64 path: v_mfma_f64_4x4x4f64 (measured on gfx950 at about 1.6x the
-// throughput of the 16x16x4 FP64 shape).  Mixed path: operands rounded to
-// FP32 while staging into LDS, v_mfma_f32_16x16x4f32 with FP32 accumulation,
-// the result added to the FP64 output in FP64.
+// so that A' B'' is the interleaved complex product.  Operands rounded to FP32
+// while staging into LDS, v_mfma_f32_16x16x4f32 with FP32 accumulation, the
+// result added to the FP64 output in FP64.
 #include "common.h"
 #include <type_traits>
+#include <utility>
 
 namespace btsq {
 
@@ -29,55 +40,23 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kBK = 16;          // complex k per LDS stage
 constexpr int kThreads = 256;    // 4 waves, 2 x 2 over the tile
 
-template <bool MIXED> struct Prec;
-// Output layout of one 16 x 16 MFMA block: lane l, accumulator register r
-// holds row row_of(l, r), real column l % 16.  Measured on gfx950: the FP64
-// instruction interleaves rows (l/16 + 4r), the FP32 one blocks them
-// (4(l/16) + r).  Inputs: A[l%16][l/16], B[l/16][l%16] for both.
-template <> struct Prec<false> {
-    typedef double2 C;
-    typedef double R;
-    typedef double Acc;
-    static constexpr int NR = 1;   // accumulator values per lane per MFMA
-    // row within the 4-row group of lane, accumulator element r
-    static __device__ inline int row_of(int lane, int r) { return lane >> 4; }
-    static __device__ inline double elem(const Acc& a, int r) { return a; }
-    static __device__ inline C cvt(double2 v) { return v; }
-    static __device__ inline R flip(R v, bool neg) {
-        return __longlong_as_double(__double_as_longlong(v) ^ (neg ? (long long)0x8000000000000000ull : 0ll));
-    }
-    static __device__ inline Acc mfma(R a, R b, Acc c) {
-        return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct Prec<true> {
-    typedef float2 C;
-    typedef float R;
-    typedef v4f Acc;
-    static constexpr int NR = 4;
-    // row within the 16-row block of lane, accumulator element r
-    static __device__ inline int row_of(int lane, int r) { return 4 * (lane >> 4) + r; }
-    static __device__ inline double elem(const Acc& a, int r) { return (double)a[r]; }
-    static __device__ inline C cvt(double2 v) { return make_float2((float)v.x, (float)v.y); }
-    static __device__ inline R flip(R v, bool neg) {
-        return __int_as_float(__float_as_int(v) ^ (neg ? (int)0x80000000u : 0));
-    }
-    static __device__ inline Acc mfma(R a, R b, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-};
-
 __device__ inline double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-__device__ inline int find_op(const GemmOp* __restrict__ ops, int nops, int bid) {
-    int lo = 0, hi = nops - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (ops[mid].tile_begin <= bid) lo = mid; else hi = mid - 1;
+// The product that owns tile bid: the last one whose first tile is not past
+// it.  The lanes of a wave look at 64 products at once, so the search is one
+// memory latency for up to 64 products (a scalar binary search is one per
+// level, about 2 us before the first operand load of a tile).
+__device__ inline int find_op(const GemmOp* __restrict__ ops, int nops, int bid, int lane) {
+    int last = 0;
+    for (int base = 0; base < nops; base += 64) {
+        const int i = min(base + lane, nops - 1);
+        const unsigned long long in = __ballot(base + lane < nops && ops[i].tile_begin <= bid);
+        if (in == 0) break;
+        last = base + 63 - __clzll(in);
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(last);
 }
 
 // Global pointer in the global address space (the C operand's loads).
@@ -127,10 +106,8 @@ struct TermAddr {
     static constexpr int NA = BM * kBK / kThreads;
     static constexpr int NB = BN * kBK / kThreads;
     __amdgpu_buffer_rsrc_t ra, rb;
-    unsigned va[NA];
-    unsigned vb[NB];
+    unsigned va[NA], vb[NB];
     int ska, skb;
-    int km1;
     StageFlags f;
 };
 
@@ -152,7 +129,6 @@ __device__ inline void term_setup(const GemmTerm& T, int m, int n, int i0, int j
     ta.f.bh = bh;
     ta.f.alpha = T.alpha;
     ta.f.akind = T.alpha.y != 0.0 ? 0 : T.alpha.x == 1.0 ? 1 : T.alpha.x == -1.0 ? 2 : 0;
-    ta.km1 = T.k - 1;
     ta.ska = (ah ? T.lda : 1) * 16;
     ta.skb = (bh ? 1 : T.ldb) * 16;
     ta.ra = ah ? operand_rsrc(T.A, T.k, m, T.lda) : operand_rsrc(T.A, m, T.k, T.lda);
@@ -173,107 +149,383 @@ __device__ inline void term_setup(const GemmTerm& T, int m, int n, int i0, int j
     }
 }
 
-// Raw operands of one stage in flight.
+// Raw operands of one stage in flight, and the flags of the term they belong to.
 template <int BM, int BN>
 struct Stage {
-    double2 ra[BM * kBK / kThreads];
-    double2 rb[BN * kBK / kThreads];
+    static constexpr int NA = BM * kBK / kThreads;
+    static constexpr int NB = BN * kBK / kThreads;
+    double2 ra[NA], rb[NB];
+    StageFlags f;
 };
 
-// Issue the global loads of one stage at k offset k0, all before any is
-// waited on, so that they overlap the MFMAs of the current stage.  Only the
-// last stage of a term whose k is not a multiple of the stage depth has
-// lanes past k; they are switched to kOOB.  With live false every lane is
-// switched to kOOB: the register set is then defined (all zeros) without
-// any memory access, so the caller can issue unconditionally and the
-// compiler never has to keep a register set's old and new values at once.
+// Where the loads stand: the term, the largest k still inside it counted from
+// the stage's first k (negative when no stage is left), and the scalar byte
+// offsets of the stage.  All wave-uniform.
+struct Fetch {
+    int t, lim, soa, sob;
+};
+
+// Steps to the stage after the current one, setting up the next term that has
+// any k when the current one ends.  The last stage of a term whose k is not a
+// multiple of the stage depth switches the lanes past k to kOOB for good (the
+// next term sets the offsets up again): lim - p < 0 exactly there, and every
+// in-range offset is below 2^31, so with the sign bit set it is at least kOOB.
+// Past the last term lim stays negative and every lane is switched off: the
+// register set is then defined (all zeros) without any memory access, so the
+// loads are issued unconditionally.  All other stages take no vector
+// arithmetic here or in load_elem.
 template <int BM, int BN>
-__device__ inline void issue_stage(const TermAddr<BM, BN>& ta, int k0, int tid, Stage<BM, BN>& st,
-                                   bool live = true) {
-    constexpr int NA = BM * kBK / kThreads;
-    constexpr int NB = BN * kBK / kThreads;
-    const int lim = live ? ta.km1 - k0 : -1;   // largest k offset inside the term
-    // wave-uniform by construction; readfirstlane lets the compiler keep them in SGPRs
-    const int soa = __builtin_amdgcn_readfirstlane(live ? k0 * ta.ska : 0);
-    const int sob = __builtin_amdgcn_readfirstlane(live ? k0 * ta.skb : 0);
-    // A lane past k gets the top bit set: lim - p < 0 exactly then, and every
-    // in-range offset is below 2^31, so the result is at least kOOB.  Plain
-    // arithmetic rather than a choice, so the issue is straight-line code.
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-        const unsigned past = (unsigned)(lim - a_p<BM>(ta.f.ah, tid + kThreads * q)) & kOOB;
-        st.ra[q] = load_b128(ta.ra, ta.va[q] | past, soa);
+__device__ inline void next_stage(const GemmTerm* terms, int nterms, int m, int n, int i0, int j0, int tid,
+                                  Fetch& f, TermAddr<BM, BN>& ta, int step = kBK) {
+    f.lim -= step;
+    f.soa += step * ta.ska;
+    f.sob += step * ta.skb;
+    if (f.lim < 0) {
+        f.soa = f.sob = 0;
+        while (f.t < nterms) {
+            if (++f.t == nterms) break;
+            if (terms[f.t].k > 0) {
+                f.lim = terms[f.t].k - 1;
+                term_setup<BM, BN>(terms[f.t], m, n, i0, j0, tid, ta);
+                break;
+            }
+        }
     }
+    if (f.lim < kBK - 1) {
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        const unsigned past = (unsigned)(lim - b_p<BN>(ta.f.bh, tid + kThreads * q)) & kOOB;
-        st.rb[q] = load_b128(ta.rb, ta.vb[q] | past, sob);
+        for (int q = 0; q < ta.NA; ++q)
+            ta.va[q] |= (unsigned)(f.lim - a_p<BM>(ta.f.ah, tid + kThreads * q)) & kOOB;
+#pragma unroll
+        for (int q = 0; q < ta.NB; ++q)
+            ta.vb[q] |= (unsigned)(f.lim - b_p<BN>(ta.f.bh, tid + kThreads * q)) & kOOB;
     }
 }
 
-// Conjugate and scale by alpha (out-of-range values are already zero).
-// Conjugation and alpha = -1 are sign flips with wave-uniform masks, so the
-// common case has no branch; only a general alpha takes the complex product.
+// Load e of a stage (A's first, then B's).
+template <int BM, int BN>
+__device__ inline void load_elem(const TermAddr<BM, BN>& ta, const Fetch& f, Stage<BM, BN>& st, int e) {
+    constexpr int NA = Stage<BM, BN>::NA;
+    // wave-uniform by construction; readfirstlane lets the compiler keep them in SGPRs
+    if (e < NA) st.ra[e] = load_b128(ta.ra, ta.va[e], __builtin_amdgcn_readfirstlane(f.soa));
+    else st.rb[e - NA] = load_b128(ta.rb, ta.vb[e - NA], __builtin_amdgcn_readfirstlane(f.sob));
+}
+
+template <int BM, int BN>
+__device__ inline void load_stage(const TermAddr<BM, BN>& ta, const Fetch& f, Stage<BM, BN>& st) {
+#pragma unroll
+    for (int e = 0; e < Stage<BM, BN>::NA + Stage<BM, BN>::NB; ++e) load_elem<BM, BN>(ta, f, st, e);
+    st.f = ta.f;
+}
+
 __device__ inline double flip_sign(double v, unsigned long long mask) {
     return __longlong_as_double(__double_as_longlong(v) ^ (long long)mask);
 }
 
+// A general alpha is multiplied into B; +1 and -1 need no arithmetic (below).
 template <int BM, int BN>
-__device__ inline void finish_stage(const StageFlags& f, Stage<BM, BN>& st) {
-    constexpr int NA = BM * kBK / kThreads;
-    constexpr int NB = BN * kBK / kThreads;
+__device__ inline void scale_stage(Stage<BM, BN>& st) {
+    if (st.f.akind == 0) {
+#pragma unroll
+        for (int q = 0; q < Stage<BM, BN>::NB; ++q) {
+            if (st.f.bh) st.rb[q].y = -st.rb[q].y;
+            st.rb[q] = cmul(st.f.alpha, st.rb[q]);
+            if (st.f.bh) st.rb[q].y = -st.rb[q].y;
+        }
+    }
+}
+
+// A stage to LDS (out-of-range values are already zero), mixed path.
+// Conjugation and alpha = -1 are sign flips with wave-uniform masks.
+template <int BM, int BN>
+__device__ inline void store_stage_mixed(int tid, const Stage<BM, BN>& st, float2 (*As)[BM + 1], float2 (*Bs)[BN + 1]) {
     constexpr unsigned long long kSign = 0x8000000000000000ull;
+    const StageFlags& f = st.f;
     const bool neg = f.akind == 2;
-    const unsigned long long ma = f.ah ? kSign : 0ull;             // Im A
-    const unsigned long long mbx = neg ? kSign : 0ull;             // Re B
-    const unsigned long long mby = f.bh != neg ? kSign : 0ull;     // Im B
+    auto cvt = [](double2 v) { return make_float2((float)v.x, (float)v.y); };
 #pragma unroll
-    for (int q = 0; q < NA; ++q) st.ra[q].y = flip_sign(st.ra[q].y, ma);
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        st.rb[q].x = flip_sign(st.rb[q].x, mbx);
-        st.rb[q].y = flip_sign(st.rb[q].y, mby);
-    }
-    if (f.akind == 0) {
-#pragma unroll
-        for (int q = 0; q < NB; ++q) st.rb[q] = cmul(f.alpha, st.rb[q]);
-    }
-}
-
-template <bool MIXED, int BM, int BN>
-__device__ inline void store_stage(const StageFlags& ta, int tid, const Stage<BM, BN>& st,
-                                   typename Prec<MIXED>::C (*As)[BM + 1],
-                                   typename Prec<MIXED>::C (*Bs)[BN + 1]) {
-    constexpr int NA = BM * kBK / kThreads;
-    constexpr int NB = BN * kBK / kThreads;
-#pragma unroll
-    for (int q = 0; q < NA; ++q) {
-        const int e = tid + kThreads * q;
-        As[a_p<BM>(ta.ah, e)][a_i<BM>(ta.ah, e)] = Prec<MIXED>::cvt(st.ra[q]);
+    for (int e = 0; e < Stage<BM, BN>::NA; ++e) {
+        const int x = tid + kThreads * e;
+        double2 v = st.ra[e];
+        v.y = flip_sign(v.y, f.ah ? kSign : 0ull);
+        As[a_p<BM>(f.ah, x)][a_i<BM>(f.ah, x)] = cvt(v);
     }
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        const int e = tid + kThreads * q;
-        Bs[b_p<BN>(ta.bh, e)][b_j<BN>(ta.bh, e)] = Prec<MIXED>::cvt(st.rb[q]);
+    for (int e = 0; e < Stage<BM, BN>::NB; ++e) {
+        const int x = tid + kThreads * e;
+        double2 v = st.rb[e];
+        v.x = flip_sign(v.x, neg ? kSign : 0ull);
+        v.y = flip_sign(v.y, f.bh != neg ? kSign : 0ull);
+        Bs[b_p<BN>(f.bh, x)][b_j<BN>(f.bh, x)] = cvt(v);
     }
 }
 
-// One workgroup computes a BM x BN complex tile; its 4 waves split the tile
-// 2 x 2 (BM/2 rows x BN real columns each, i.e. row groups x BN/16 MFMA
-// column blocks).
+// FP64 path: where the elements of a stage go in an LDS buffer (byte offsets;
+// they depend on which operands are read transposed only, so they are set up
+// again only when that changes).
+template <int BM, int BN>
+struct LdsPlace {
+    static constexpr int NA = Stage<BM, BN>::NA;
+    static constexpr int NB = Stage<BM, BN>::NB;
+    unsigned a[NA], b[NB];
+    int layout = -1;
+    __device__ inline void set(const StageFlags& f, int tid) {
+        const int want = (f.ah ? 1 : 0) | (f.bh ? 2 : 0);
+        if (want == layout) return;
+        layout = want;
+#pragma unroll
+        for (int e = 0; e < NA; ++e) {
+            const int x = tid + kThreads * e;
+            a[e] = (a_p<BM>(f.ah, x) * (BM + 1) + a_i<BM>(f.ah, x)) * 16;
+        }
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const int x = tid + kThreads * e;
+            b[e] = (b_p<BN>(f.bh, x) * (BN + 1) + b_j<BN>(f.bh, x)) * 16;
+        }
+    }
+    __device__ inline void store(const Stage<BM, BN>& st, double2 (*As)[BM + 1], double2 (*Bs)[BN + 1], int e) const {
+        if (e < NA) *reinterpret_cast<double2*>(reinterpret_cast<char*>(As) + a[e]) = st.ra[e];
+        else *reinterpret_cast<double2*>(reinterpret_cast<char*>(Bs) + b[e - NA]) = st.rb[e - NA];
+    }
+};
+
+// Conjugates what the stage's operands take as H.  (alpha = -1 costs nothing
+// here: the accumulators change sign between terms instead.)
+template <int BM, int BN>
+__device__ inline void conj_stage(Stage<BM, BN>& st) {
+    constexpr unsigned long long kSign = 0x8000000000000000ull;
+    if (st.f.ah) {
+#pragma unroll
+        for (int q = 0; q < Stage<BM, BN>::NA; ++q) st.ra[q].y = flip_sign(st.ra[q].y, kSign);
+    }
+    if (st.f.bh) {
+#pragma unroll
+        for (int q = 0; q < Stage<BM, BN>::NB; ++q) st.rb[q].y = flip_sign(st.rb[q].y, kSign);
+    }
+}
+
+// The accumulators of one wave and what it does with them: start (beta C),
+// the multiply-adds of one LDS stage, and the store of its part of the tile.
+// The 4 waves of a workgroup split the BM x BN complex tile 2 x 2.
+template <bool MIXED, int BM, int BN> struct WaveTile;
+
+// FP64: v_mfma_f64_16x16x4 on planar operands.  A lane reads its entry of A
+// and B as one (re, im) pair, and a 16 x 16 x 4 complex block is
+//     Re += Re A Re B - Im A Im B,   Im += Re A Im B + Im A Re B,
+// four MFMAs on the two components; the minus sign is the instruction's
+// negation of its first operand.  Layout (measured on gfx950): A[l%16][l/16],
+// B[l/16][l%16], D row l/16 + 4r, column l%16 in register r.
+template <int BM, int BN>
+struct WaveTile<false, BM, BN> {
+    static constexpr int RA = BM / 32;    // 16-row blocks of the wave
+    static constexpr int CB = BN / 32;    // 16-column blocks of the wave
+    v4d re[RA][CB], im[RA][CB];
+
+    static __device__ inline v4d mfma(double a, double b, v4d c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ inline v4d mfma_nega(double a, double b, v4d c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
+    }
+
+    // Starts at beta C (C read before any of D is written, so C may be D), so
+    // the epilogue only stores.
+    __device__ inline void init(const GemmOp* op, int m, int n, int i0, int j0, int lane) {
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) re[a][b] = im[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+        if (!op->C) return;
+        const gptr_t Cp = (gptr_t)op->C;
+        const int ldc = op->ldc;
+        const double2 beta = op->beta;
+        double2 cv[RA][CB][4];
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = min(i0 + a * 16 + 4 * r + (lane >> 4), m - 1);
+                    const int col = min(j0 + b * 16 + (lane & 15), n - 1);
+                    cv[a][b][r] = Cp[(size_t)row * ldc + col];
+                }
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double2 c = cv[a][b][r];
+                    re[a][b][r] = beta.x * c.x - beta.y * c.y;
+                    im[a][b][r] = beta.x * c.y + beta.y * c.x;
+                }
+    }
+
+    __device__ inline void negate() {
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    re[a][b][r] = -re[a][b][r];
+                    im[a][b][r] = -im[a][b][r];
+                }
+    }
+
+    // The wave's entries of one 4-deep k step: 16 x 4 blocks of A, 4 x 16 of B.
+    struct Frag {
+        double2 a[RA], b[CB];
+    };
+    static constexpr int kReads = RA + CB;
+    static constexpr int kMfma = 4 * RA * CB;
+
+    // read e of the fragment of step kk
+    static __device__ inline void read(Frag& f, const double2 (*As)[BM + 1], const double2 (*Bs)[BN + 1], int r0,
+                                       int c0, int lane, int kk, int e) {
+        const int p = 4 * kk + (lane >> 4), q = lane & 15;
+        if (e < RA) f.a[e] = As[p][r0 + e * 16 + q];
+        else f.b[e - RA] = Bs[p][c0 + (e - RA) * 16 + q];
+    }
+
+    // The MFMAs of one step, with hook(i) run after the i-th: reads, loads and
+    // LDS stores put there issue while the matrix core works (64 cycles per
+    // MFMA), where in a block of their own they would leave it idle.
+    template <class H>
+    __device__ inline void step(const Frag& f, H hook) {
+#pragma unroll
+        for (int i = 0; i < kMfma; ++i) {
+            const int half = i / (2 * RA * CB), j = i % (2 * RA * CB);
+            const int b = j / (2 * RA), a = (j / 2) % RA;
+            if (half == 0) {
+                if (j & 1) im[a][b] = mfma(f.a[a].x, f.b[b].y, im[a][b]);
+                else re[a][b] = mfma(f.a[a].x, f.b[b].x, re[a][b]);
+            } else {
+                if (j & 1) im[a][b] = mfma(f.a[a].y, f.b[b].x, im[a][b]);
+                else re[a][b] = mfma_nega(f.a[a].y, f.b[b].y, re[a][b]);
+            }
+            hook(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    __device__ inline void store(const GemmOp* op, int m, int n, int i0, int j0, int lane) {
+        double2* D = op->D;
+        const int ldd = op->ldd;
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = i0 + a * 16 + 4 * r + (lane >> 4);
+                    const int col = j0 + b * 16 + (lane & 15);
+                    if (row < m && col < n) D[(size_t)row * ldd + col] = make_double2(re[a][b][r], im[a][b][r]);
+                }
+    }
+};
+
+// Mixed: operands rounded to FP32 in LDS, v_mfma_f32_16x16x4f32 on the 2 x 2
+// real embedding above, FP32 accumulation, beta C added in FP64 at the end.
+template <int BM, int BN>
+struct WaveTile<true, BM, BN> {
+    static constexpr int RG = BM / 32;    // 16-row blocks of the wave
+    static constexpr int NI = BN / 16;    // 16-column blocks of the wave (real columns)
+    v4f acc[RG][NI];
+
+    __device__ inline void init(const GemmOp*, int, int, int, int, int) {
+#pragma unroll
+        for (int a = 0; a < RG; ++a)
+#pragma unroll
+            for (int b = 0; b < NI; ++b) acc[a][b] = v4f{};
+    }
+
+    __device__ inline void stage(const float2 (*As)[BM + 1], const float2 (*Bs)[BN + 1], int r0, int c0, int lane) {
+        const int cA = (lane >> 4) & 1;   // real k within the pair: 0 = re part of A, 1 = im part
+        const int pOff = lane >> 5;       // complex k offset within the 4-wide real k step
+        const int r16 = lane & 15;
+        const int d = lane & 1;           // output component of this lane's B'' column
+        const int negB = cA == 1 && d == 0 ? (int)0x80000000u : 0;
+#pragma unroll
+        for (int kk = 0; kk < kBK / 2; ++kk) {
+            const int p = 2 * kk + pOff;
+            float av[RG], bv[NI];
+            // one component read per operand: A' takes component cA, B'' takes
+            // component cA ^ d, negated for (cA, d) = (1, 0)
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+                av[g] = reinterpret_cast<const float*>(&As[p][r0 + g * 16 + r16])[cA];
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const float v = reinterpret_cast<const float*>(&Bs[p][c0 + ((ni * 16 + r16) >> 1)])[cA ^ d];
+                bv[ni] = __int_as_float(__float_as_int(v) ^ negB);
+            }
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    acc[g][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g], bv[ni], acc[g][ni], 0, 0, 0);
+        }
+    }
+
+    // Lane holds real column lane%16 (component lane%2 of complex column
+    // lane%16 / 2) of rows 4 (lane/16) + r of each 16-row block.
+    __device__ inline void store(const GemmOp* op, int m, int n, int i0, int j0, int lane) {
+        double* D = reinterpret_cast<double*>(op->D);
+        const int ldd = op->ldd, ldc = op->ldc;
+        const double2 beta = op->beta;
+        const int d = lane & 1, rq = 4 * (lane >> 4), cq = lane & 15;
+        double2 cv[RG][NI][4];
+        if (op->C) {
+            // all C loads first (clamped, unconditional), then the stores
+            const gptr_t Cp = (gptr_t)op->C;
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = min(i0 + g * 16 + rq + r, m - 1);
+                        const int col = min(j0 + ((ni * 16 + cq) >> 1), n - 1);
+                        cv[g][ni][r] = Cp[(size_t)row * ldc + col];
+                    }
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        asm volatile("" : "+v"(cv[g][ni][r].x), "+v"(cv[g][ni][r].y));
+        }
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = i0 + g * 16 + rq + r;
+                    const int col = j0 + ((ni * 16 + cq) >> 1);
+                    double v = (double)acc[g][ni][r];
+                    if (op->C) {
+                        const double2 c = cv[g][ni][r];
+                        v += d ? (beta.x * c.y + beta.y * c.x) : (beta.x * c.x - beta.y * c.y);
+                    }
+                    if (row < m && col < n) D[2 * ((size_t)row * ldd + col) + d] = v;
+                }
+    }
+};
+
+// One workgroup computes a BM x BN complex tile of one product.
 template <bool MIXED, int BM, int BN>
 __global__ __launch_bounds__(kThreads)
 void zgemm_grouped(const GemmOp* __restrict__ ops, int nops) {
-    typedef typename Prec<MIXED>::C CT;
-    typedef typename Prec<MIXED>::R RT;
-    typedef typename Prec<MIXED>::Acc AccT;
-    constexpr int MI = BM / 32;
-    constexpr int NI = BN / 16;
+    typedef typename std::conditional<MIXED, float2, double2>::type CT;     // element in LDS
     __shared__ CT As[2][kBK][BM + 1];
     __shared__ CT Bs[2][kBK][BN + 1];
 
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
-    const GemmOp* op = ops + find_op(ops, nops, bid);
+    const GemmOp* op = ops + find_op(ops, nops, bid, threadIdx.x & 63);
     const int m = op->m, n = op->n, nterms = op->nterms;
     const int local = bid - op->tile_begin;
     const int tm = local / op->tiles_n, tn = local - tm * op->tiles_n;
@@ -282,206 +534,137 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, int nops) {
     const GemmTerm* terms = op->t;     // uniform: read with scalar loads
 
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
-    const int cA = (lane >> 4) & 1;   // real k within the pair: 0 = re part of A, 1 = im part
-    const int pOff = lane >> 5;       // complex k offset within the 4-wide real k step
-    const int r16 = lane & 15;
-    const int d = lane & 1;           // output component of this lane's B'' column
-    const bool negB = cA == 1 && d == 0;
+    const int r0 = (wave & 1) * (BM / 2), c0 = (wave >> 1) * (BN / 2);   // the wave's part of the tile
+    WaveTile<MIXED, BM, BN> wt;
+    wt.init(op, m, n, i0 + r0, j0 + c0, lane);
 
-    // FP64: v_mfma_f64_4x4x4f64 with A replicated over its four blocks acts as
-    // a 4-row x 16-column x 4-k product: A[row = lane%4][k = lane/16],
-    // B[k = lane/16][col = lane%16], D[row = lane/16][col = lane%16] (layout
-    // measured on gfx950).  A wave covers BM/2 rows as RG groups of 4 rows.
-    // FP32 (mixed): v_mfma_f32_16x16x4f32, MI blocks of 16 rows.
-    constexpr int RG = MIXED ? MI : BM / 8;
-    AccT acc[RG][NI];
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-        for (int b = 0; b < NI; ++b)
-            acc[a][b] = AccT{};
-    if constexpr (!MIXED) {
-        // FP64: the accumulators start at beta C (C read before any of D is
-        // written, so C may be D), and the epilogue only stores.
-        if (op->C) {
-            const gptr_t Cp = (gptr_t)op->C;
-            const int ldc = op->ldc;
-            const double2 beta = op->beta;
-            double2 cv[RG][NI];
-#pragma unroll
-            for (int g = 0; g < RG; ++g)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    const int row = min(i0 + wm * (BM / 2) + g * 4 + (lane >> 4), m - 1);
-                    const int col = min(j0 + ((wn * BN + ni * 16 + r16) >> 1), n - 1);
-                    cv[g][ni] = Cp[(size_t)row * ldc + col];
-                }
-#pragma unroll
-            for (int g = 0; g < RG; ++g)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    const double2 c = cv[g][ni];
-                    acc[g][ni] = d ? (beta.x * c.y + beta.y * c.x) : (beta.x * c.x - beta.y * c.y);
-                }
-        }
-    }
-
-    // Stages are (term, k offset) pairs in order; next() steps to the
-    // following one, skipping empty terms.  Two register sets hold the raw
-    // operands of the next two stages: each step first issues the loads of
-    // the stage after next (setting up that stage's term when it starts a
-    // new one), then runs the MFMAs of the stage in LDS, then converts the
-    // next stage's operands (waiting for their loads) into the other LDS
-    // buffer.  Each register set carries the flags of the term it was
-    // loaded for.
-    auto next = [&](int& t, int& k0) {
-        k0 += kBK;
-        while (t < nterms && k0 >= terms[t].k) { ++t; k0 = 0; }
-    };
-    int t1 = 0, k1 = 0;
-    while (t1 < nterms && terms[t1].k <= 0) ++t1;
+    // Stages are the terms' k ranges in order, kBK at a time.  Two register
+    // sets hold the raw operands of the next two stages: while the stage in LDS
+    // is multiplied, the loads of the stage after next are issued into one set
+    // and the other set (loaded during the stage before) goes to the other LDS
+    // buffer.
     Stage<BM, BN> st[2];
-    StageFlags sf[2];
     TermAddr<BM, BN> ta;
-    int ta_term = -1;
-    bool cur = false, fly = false;
-    if (t1 < nterms) {
-        term_setup<BM, BN>(terms[t1], m, n, i0, j0, tid, ta);
-        ta_term = t1;
-        issue_stage<BM, BN>(ta, k1, tid, st[0]);
-        finish_stage<BM, BN>(ta.f, st[0]);
-        store_stage<MIXED, BM, BN>(ta.f, tid, st[0], As[0], Bs[0]);
-        cur = true;
-        next(t1, k1);
-        fly = t1 < nterms;
-        if (fly && t1 != ta_term) { term_setup<BM, BN>(terms[t1], m, n, i0, j0, tid, ta); ta_term = t1; }
-        issue_stage<BM, BN>(ta, k1, tid, st[1], fly);
-        sf[1] = ta.f;
+    ta.ska = ta.skb = 0;
+    Fetch fe{-1, -1, 0, 0};
+    next_stage<BM, BN>(terms, nterms, m, n, i0, j0, tid, fe, ta, 0);
+    bool cur = fe.lim >= 0, fly = false;
+    if (cur) {
+        load_stage<BM, BN>(ta, fe, st[0]);
+        next_stage<BM, BN>(terms, nterms, m, n, i0, j0, tid, fe, ta);
+        fly = fe.lim >= 0;
+        load_stage<BM, BN>(ta, fe, st[1]);
+        scale_stage<BM, BN>(st[0]);
     }
-    __syncthreads();
-    int buf = 0;
+    constexpr int NL = Stage<BM, BN>::NA + Stage<BM, BN>::NB;
 
-    // one stage: X = register set in flight (the next stage), Y = free set
-    auto step = [&](auto xs) {
-        constexpr int X = decltype(xs)::value, Y = 1 - X;
-        int t2 = t1, k2 = k1;
-        bool fly2 = false;
-        if (fly) {
-            next(t2, k2);
-            fly2 = t2 < nterms;
-        }
-        if (fly2 && t2 != ta_term) { term_setup<BM, BN>(terms[t2], m, n, i0, j0, tid, ta); ta_term = t2; }
-        issue_stage<BM, BN>(ta, k2, tid, st[Y], fly2);
-        sf[Y] = ta.f;
-        // keep the order issue -> MFMAs -> conversion of the next stage, so
-        // that the loads in flight have a whole stage of MFMAs to land
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < kBK / 2; ++kk) {
-            const int p = 2 * kk + pOff;
-            RT av[RG], bv[NI];
-            // one component read per operand: A' takes component cA, B'' takes
-            // component cA ^ d, negated for (cA, d) = (1, 0)
-#pragma unroll
-            for (int g = 0; g < RG; ++g) {
-                const int row = MIXED ? (wm * (BM / 2) + g * 16 + r16) : (wm * (BM / 2) + g * 4 + (lane & 3));
-                av[g] = reinterpret_cast<const RT*>(&As[buf][p][row])[cA];
-            }
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                const int jc = (wn * BN + ni * 16 + r16) >> 1;
-                const RT v = reinterpret_cast<const RT*>(&Bs[buf][p][jc])[cA ^ d];
-                bv[ni] = Prec<MIXED>::flip(v, negB);
-            }
-#pragma unroll
-            for (int g = 0; g < RG; ++g)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
-                    acc[g][ni] = Prec<MIXED>::mfma(av[g], bv[ni], acc[g][ni]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // unconditional like the issue: without a next stage st[X] holds
-        // zeros from kOOB loads, stored to the buffer no later stage reads
-        finish_stage<BM, BN>(sf[X], st[X]);
-        store_stage<MIXED, BM, BN>(sf[X], tid, st[X], As[buf ^ 1], Bs[buf ^ 1]);
+    if constexpr (MIXED) {
+        if (cur) store_stage_mixed<BM, BN>(tid, st[0], As[0], Bs[0]);
         __syncthreads();
-        cur = fly;
-        fly = fly2;
-        t1 = t2;
-        k1 = k2;
-        buf ^= 1;
-    };
-    // FP64: four steps per iteration.  The compiler's wait counts throttle
-    // the load issue only in the first bodies after the loop header, so the
-    // longer body keeps the loads two stages ahead in the others.  (The mixed
-    // kernels keep two: four would cost them occupancy.)
-    while (cur) {
-        step(std::integral_constant<int, 1>{});
-        if (!cur) break;
-        step(std::integral_constant<int, 0>{});
-        if constexpr (!MIXED) {
-            if (!cur) break;
+        // one stage: X = register set in flight (the next stage), Y = free set,
+        // X - 1 the parity of the LDS buffer multiplied
+        auto step = [&](auto xs) {
+            constexpr int X = decltype(xs)::value, Y = 1 - X, buf = Y;
+            next_stage<BM, BN>(terms, nterms, m, n, i0, j0, tid, fe, ta);
+            load_stage<BM, BN>(ta, fe, st[Y]);
+            // keep the order issue -> MFMAs -> conversion of the next stage, so
+            // that the loads in flight have a whole stage of MFMAs to land
+            __builtin_amdgcn_sched_barrier(0);
+            wt.stage(As[buf], Bs[buf], r0, c0, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            // unconditional like the loads: without a next stage st[X] holds
+            // zeros from kOOB loads, stored to the buffer no later stage reads
+            scale_stage<BM, BN>(st[X]);
+            store_stage_mixed<BM, BN>(tid, st[X], As[buf ^ 1], Bs[buf ^ 1]);
+            __syncthreads();
+            cur = fly;
+            fly = fe.lim >= 0;
+        };
+        while (cur) {
             step(std::integral_constant<int, 1>{});
             if (!cur) break;
             step(std::integral_constant<int, 0>{});
         }
+    } else {
+        // FP64: memory and LDS instructions run in the shadow of the MFMAs (64
+        // cycles each).  Vector arithmetic does not: every place between two
+        // MFMAs with any of it cost about one MFMA (a stage with address and
+        // sign arithmetic at its 8 loads and 8 stores took 5600 cycles for 4096
+        // of MFMAs), so the stage has one, which conjugates.  The first three k steps
+        // of a stage carry the loads of the stage after next and the LDS stores
+        // of the next one; the barrier comes before the last step, whose
+        // operands are in registers by then, so that step's MFMAs cover the
+        // first reads of the next stage.
+        typedef WaveTile<MIXED, BM, BN> WT;
+        constexpr int KS = kBK / 4, NR = WT::kReads, NM = WT::kMfma;
+        typename WT::Frag fr[2];
+        LdsPlace<BM, BN> place;
+        bool neg = false, neg_lds = false;    // sign of the accumulators / of the stage in LDS
+        if (cur) {
+            place.set(st[0].f, tid);
+            neg_lds = st[0].f.akind == 2;
+            conj_stage<BM, BN>(st[0]);
+#pragma unroll
+            for (int e = 0; e < NL; ++e) place.store(st[0], As[0], Bs[0], e);
+        }
+        __syncthreads();
+        if (cur) {
+#pragma unroll
+            for (int e = 0; e < NR; ++e) WT::read(fr[0], As[0], Bs[0], r0, c0, lane, 0, e);
+        }
+        auto step = [&](auto xs) {
+            constexpr int X = decltype(xs)::value, Y = 1 - X, buf = Y;
+            next_stage<BM, BN>(terms, nterms, m, n, i0, j0, tid, fe, ta);
+            if (neg_lds != neg) {
+                neg = neg_lds;
+                wt.negate();
+            }
+            neg_lds = st[X].f.akind == 2;
+            place.set(st[X].f, tid);
+            st[Y].f = ta.f;
+            __builtin_amdgcn_sched_barrier(0);
+            auto kstep = [&](auto ks) {
+                constexpr int kk = decltype(ks)::value;
+                if constexpr (kk == KS - 1) {
+                    __syncthreads();
+                    wt.step(fr[kk & 1], [&](int i) {
+                        if (i < NR) WT::read(fr[(kk + 1) & 1], As[buf ^ 1], Bs[buf ^ 1], r0, c0, lane, 0, i);
+                    });
+                } else {
+                    if constexpr (kk == 1) {
+                        scale_stage<BM, BN>(st[X]);
+                        conj_stage<BM, BN>(st[X]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // after MFMA i: the next step's reads first; load e at slot
+                    // (e + 1/2) / NL of the three steps, store e at e / NL of the
+                    // last two
+                    wt.step(fr[kk & 1], [&](int i) {
+                        if (i < NR) WT::read(fr[(kk + 1) & 1], As[buf], Bs[buf], r0, c0, lane, kk + 1, i);
+                        const int slot = kk * NM + i;
+#pragma unroll
+                        for (int e = 0; e < NL; ++e) {
+                            if ((2 * e + 1) * (KS - 1) * NM / (2 * NL) == slot) load_elem<BM, BN>(ta, fe, st[Y], e);
+                            if (NM + e * (KS - 2) * NM / NL == slot) place.store(st[X], As[buf ^ 1], Bs[buf ^ 1], e);
+                        }
+                    });
+                }
+            };
+            [&]<int... K>(std::integer_sequence<int, K...>) {
+                (kstep(std::integral_constant<int, K>{}), ...);
+            }(std::make_integer_sequence<int, KS>{});
+            cur = fly;
+            fly = fe.lim >= 0;
+        };
+        while (cur) {
+            step(std::integral_constant<int, 1>{});
+            if (!cur) break;
+            step(std::integral_constant<int, 0>{});
+        }
+        if (neg) wt.negate();
     }
 
-    // Epilogue: lane holds real column lane%16 (component lane%2 of complex
-    // column lane%16 / 2) of rows row_of(lane, r) of each row group.
-    constexpr int GR = MIXED ? 16 : 4;             // rows per row group
-    constexpr int NR = Prec<MIXED>::NR;
-    double* D = reinterpret_cast<double*>(op->D);
-    const double2* C = op->C;
-    const int ldd = op->ldd, ldc = op->ldc;
-    const double2 beta = op->beta;
-    if (MIXED && C) {
-        // all C loads first (clamped, unconditional), then the stores
-        double2 cv[RG][NI][NR];
-        const gptr_t Cp = (gptr_t)C;
-#pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int row = min(i0 + wm * (BM / 2) + g * GR + Prec<MIXED>::row_of(lane, r), m - 1);
-                    const int col = min(j0 + ((wn * BN + ni * 16 + r16) >> 1), n - 1);
-                    cv[g][ni][r] = Cp[(size_t)row * ldc + col];
-                }
-#pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-                    asm volatile("" : "+v"(cv[g][ni][r].x), "+v"(cv[g][ni][r].y));
-#pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int row = i0 + wm * (BM / 2) + g * GR + Prec<MIXED>::row_of(lane, r);
-                    const int col = j0 + ((wn * BN + ni * 16 + r16) >> 1);
-                    const double2 c = cv[g][ni][r];
-                    const double v = Prec<MIXED>::elem(acc[g][ni], r) +
-                        (d ? (beta.x * c.y + beta.y * c.x) : (beta.x * c.x - beta.y * c.y));
-                    if (row < m && col < n) D[2 * ((size_t)row * ldd + col) + d] = v;
-                }
-    } else {
-#pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int row = i0 + wm * (BM / 2) + g * GR + Prec<MIXED>::row_of(lane, r);
-                    const int col = j0 + ((wn * BN + ni * 16 + r16) >> 1);
-                    if (row < m && col < n) D[2 * ((size_t)row * ldd + col) + d] = Prec<MIXED>::elem(acc[g][ni], r);
-                }
-    }
+    wt.store(op, m, n, i0 + r0, j0 + c0, lane);
 }
 
 // Tile shapes of the grouped product (complex rows x complex columns).

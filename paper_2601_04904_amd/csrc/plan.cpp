@@ -950,8 +950,7 @@ GemmOp make_gemm_op(const OpRec& o) {
 // size class of its largest output (log2 of max(m, n), 5..10) and the class of
 // its work (log2 of its 64 x 32 tile count, 0..13); the shape comes from the
 // tuning table (filled by bt_si_sq_autotune or loaded with
-// bt_si_sq_tune_table) or, for classes never tuned, from the default rule:
-// 32 x 32 tiles below 512 tiles of 64 x 32, 64 x 32 tiles above.
+// bt_si_sq_tune_table) or, for classes never tuned, from the default rule.
 constexpr int kMClasses = 6, kTClasses = 14;
 std::atomic<int> g_tune[2][kMClasses][kTClasses];
 std::once_flag g_tune_once;
@@ -968,14 +967,34 @@ int log2_class(long v, int lo, int hi) {
     return std::min(std::max(c, lo), hi) - lo;
 }
 
-int default_shape(long tiles64x32) { return tiles64x32 < 512 ? 0 : 1; }
+// Default rule.  Mixed: 32 x 32 tiles below 512 tiles of 64 x 32, 64 x 32
+// tiles above.  FP64: the shape of smallest estimated time.  A launch is
+// bound by the CU with the most tiles, r = ceil(tiles / 256) of them; measured
+// on launches of 1 to 64 square products with r from 1 to 64, the time in us
+// at k = 512 is within 8% of 20.5 r + 4 (32 x 32), 33 r + 10 (64 x 32) and
+// 61.5 r + 16 (64 x 64), so the small tile wins while it leaves fewer CUs with
+// a last tile to themselves (3 products of 512: 62, 76 and 73 us) and the
+// large one when there are many rounds (32 products: 649, 529 and 493 us).
+int default_shape(int mixed, const long* tiles) {
+    if (mixed) return tiles[1] < 512 ? 0 : 1;
+    constexpr double kPerTile[kGemmShapes] = {20.5, 33.0, 61.5}, kFixed[kGemmShapes] = {4.0, 10.0, 16.0};
+    constexpr long kCUs = 256;
+    int best = 0;
+    double tb = 0.0;
+    for (int sh = 0; sh < kGemmShapes; ++sh) {
+        const double t = kPerTile[sh] * (double)((tiles[sh] + kCUs - 1) / kCUs) + kFixed[sh];
+        if (sh == 0 || t < tb) { best = sh; tb = t; }
+    }
+    return best;
+}
 
-int pick_shape(int mixed, int maxdim, long tiles64x32) {
+// tiles: the launch's tile count in each shape
+int pick_shape(int mixed, int maxdim, const long* tiles) {
     tune_init();
     const int mc = log2_class(maxdim, 5, 5 + kMClasses - 1);
-    const int tc = log2_class(std::max(1L, tiles64x32), 0, kTClasses - 1);
+    const int tc = log2_class(std::max(1L, tiles[1]), 0, kTClasses - 1);
     const int v = g_tune[mixed ? 1 : 0][mc][tc].load();
-    return (v >= 0 && v < kGemmShapes) ? v : default_shape(tiles64x32);
+    return (v >= 0 && v < kGemmShapes) ? v : default_shape(mixed, tiles);
 }
 
 void set_shape(Program& pg, Launch& L, int shape) {
@@ -991,14 +1010,14 @@ void set_shape(Program& pg, Launch& L, int shape) {
 }
 
 void assign_shape(Program& pg, Launch& L) {
-    long t1 = 0;
+    long tiles[kGemmShapes] = {};
     int maxdim = 1;
     for (int i = 0; i < L.count; ++i) {
         const GemmOp& g = pg.gemm[L.off + i];
-        t1 += gemm_tiles_shape(g.m, g.n, 1);
+        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] += gemm_tiles_shape(g.m, g.n, sh);
         maxdim = std::max(maxdim, std::max(g.m, g.n));
     }
-    set_shape(pg, L, pick_shape(L.mixed, maxdim, t1));
+    set_shape(pg, L, pick_shape(L.mixed, maxdim, tiles));
 }
 
 AddOp make_add_op(const OpRec& o) {
@@ -2357,7 +2376,11 @@ bt_status bt_si_sq_diag_gemm(int32_t m, int32_t n, int32_t k,
     g.m = m;
     g.n = n;
     g.nterms = k > 0 ? 1 : 0;
-    if (shape < 0) shape = pick_shape(mixed, std::max(m, n), gemm_tiles_shape(m, n, 1));
+    if (shape < 0) {
+        long tiles[kGemmShapes];
+        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] = gemm_tiles_shape(m, n, sh);
+        shape = pick_shape(mixed, std::max(m, n), tiles);
+    }
     g.tiles_n = gemm_tiles_n_shape(n, shape);
     g.tile_begin = 0;
     g.mixed = mixed;
