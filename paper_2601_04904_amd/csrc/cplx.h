@@ -11,6 +11,11 @@ __device__ inline double2 cmul_i(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
+// -a b
+__device__ inline double2 cmul_neg(double2 a, double2 b) {
+    return make_double2(fma(a.y, b.y, -(a.x * b.x)), -fma(a.x, b.y, a.y * b.x));
+}
+
 // c ? a : b on values (a conditional over two double2 lvalues would select
 // an address and keep the register arrays it points into out of registers)
 __device__ inline double2 sel2(bool c, double2 a, double2 b) {
@@ -32,14 +37,14 @@ __device__ inline void cfms(double2& acc, double2 a, double2 b) {
     acc.y = fma(-a.y, b.x, acc.y);
 }
 
-// 1 / v = conj(v) / |v|^2.  v is first scaled by a power of two so that its
-// larger component lies in [0.5, 1), which puts |v|^2 in [0.25, 2); the
-// reciprocal of |v|^2 is the hardware estimate refined by two Newton steps
+// 1 / v = conj(v) / |v|^2.  v is first scaled by a power of two so that
+// |re| + |im| lies in [0.5, 1), which puts |v|^2 in [0.125, 1); the reciprocal of |v|^2 is the hardware estimate refined by two Newton steps
 // r <- r (2 - s r) (each at least doubles the number of correct bits).  A
 // zero, infinite or NaN v gives a NaN result, which the caller flags.
 __device__ inline double2 crecip(double2 v) {
     int e;
-    (void)frexp(fmax(fabs(v.x), fabs(v.y)), &e);
+    const double m = fabs(v.x) + fabs(v.y);
+    (void)frexp(m <= DBL_MAX ? m : DBL_MAX, &e);
     const double a = ldexp(v.x, -e), b = ldexp(v.y, -e);
     const double s = fma(a, a, b * b);
     double r = __builtin_amdgcn_rcp(s);
@@ -81,6 +86,16 @@ __device__ inline unsigned pivot_key(double2 v, int row) {
     if (!(m <= DBL_MAX)) m = DBL_MAX;
     const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
     return ((unsigned)(bits >> 41) << 10) | (unsigned)(1023 - row);
+}
+
+// The same key from a row's mask and row bits (both 0 for a row that is not a
+// candidate).  A non-finite value keeps the largest exponent, so it is chosen and
+// its reciprocal is NaN, which the caller flags.
+constexpr unsigned kKeyBits = ~1023u;
+__device__ inline unsigned key_row_bits(int row) { return (unsigned)(1023 - row); }
+__device__ inline unsigned pivot_key(double2 v, unsigned mask, unsigned row_bits) {
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(fabs(v.x) + fabs(v.y));
+    return ((unsigned)(bits >> 31) & mask) | row_bits;
 }
 
 __device__ inline int key_row(unsigned key) { return 1023 - (int)(key & 1023u); }

@@ -48,7 +48,8 @@ int gemm_tiles_shape(int m, int n, int shape);
 int gemm_tiles_n_shape(int n, int shape);
 int gemm_shape_bm(int shape);
 int gemm_shape_bn(int shape);
-int inv_variant(int d);   // panel kernel shape for dimension d: 0 (256 x 1 rows), 1 (256 x 2), 2 (512 x 2)
+int inv_steps(int d);     // launches of an inverse of dimension d
+int inv_variant(int d);   // kernel shape for dimension d, 0 .. kInvVariants - 1
 hipError_t launch_inv_step(const InvJob* d_jobs, int njobs, int variant, int panel, int maxd,
                            DevStatus* status, hipStream_t s);
 hipError_t launch_add(const AddOp* d_ops, int nops, size_t max_elems, hipStream_t s);
@@ -1141,21 +1142,20 @@ Program compile(std::vector<OpRec>& ops, int nlevels, char* inv_pool) {
                 }
                 pg.inv_scratch_bytes = std::max(pg.inv_scratch_bytes, poff + 256);
                 const int nj = (int)invs.size();
-                int vcount[3] = {0, 0, 0}, vmaxd[3] = {0, 0, 0};
+                int vcount[kInvVariants] = {}, vmaxd[kInvVariants] = {};
                 for (int i : invs) {
                     const int v = inv_variant(ops[i].D.r);
                     ++vcount[v];
                     vmaxd[v] = std::max(vmaxd[v], ops[i].D.r);
                 }
-                // one launch per panel and kernel shape, plus the one that applies
-                // the last panel and writes the results; the first carries the
-                // wait on the other stream
-                const int npanels = (maxd + kInvNB - 1) / kInvNB;
+                // per kernel shape: one launch for small blocks, else one per panel
+                // plus the one that applies the last panel and writes the results;
+                // the first carries the wait on the other stream
                 bool first_launch = true;
-                for (int p = 0; p <= npanels; ++p) {
+                for (int p = 0; p < inv_steps(maxd); ++p) {
                     size_t off = first;
-                    for (int v = 0; v < 3; ++v) {
-                        if (vcount[v] > 0 && p <= (vmaxd[v] + kInvNB - 1) / kInvNB) {
+                    for (int v = 0; v < kInvVariants; ++v) {
+                        if (vcount[v] > 0 && p < inv_steps(vmaxd[v])) {
                             pg.launches.push_back(mk(6, off, vcount[v], vmaxd[v], 0, v, p, 0, cls, L,
                                                      first_launch ? wait : -1));
                             first_launch = false;
@@ -1252,6 +1252,11 @@ Program compile(std::vector<OpRec>& ops, int nlevels, char* inv_pool) {
             for (int q = 0; q < L.count; ++q) {
                 const InvJob& j = pg.inv[L.off + q];
                 const int np = (j.d + kInvNB - 1) / kInvNB;
+                if (inv_steps(j.d) == 1) {
+                    L.flops += 8.0 * (double)j.d * j.d * j.d;
+                    L.bytes += 32.0 * (double)j.d * j.d;
+                    continue;
+                }
                 if (L.panel > np) continue;
                 const double pnc = L.panel > 0 ? std::min(kInvNB, j.d - (L.panel - 1) * kInvNB) : 0;
                 const double nc = L.panel < np ? std::min(kInvNB, j.d - L.panel * kInvNB) : 0;

@@ -1,0 +1,101 @@
+"""The product and inverse kernels at the sizes where their shapes change.
+
+Products: k around the 16-deep stage, sizes around the tiles, every operand
+order with alpha = -1 and a general alpha (the accumulators change sign between
+terms of different sign; a general alpha is multiplied into an operand), and a
+launch with more products than one 64-lane search covers.  Inverses: dimensions
+around each kernel shape, with rows that force pivoting.  Tolerances: a product
+of k terms in FP64 is within (k + 4) eps of sum |a||b|; an inverse with partial
+pivoting is held to 50 eps sqrt(d) cond, as the other inverse tests.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -52
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+def crand(rng, *shape):
+    return rng.normal(size=shape) + 1j * rng.normal(size=shape)
+
+
+@pytest.mark.parametrize("k", [1, 4, 15, 16, 17, 31, 32, 33, 47, 49])
+@pytest.mark.parametrize("m,n", [(1, 65), (63, 31), (64, 64), (66, 33)])
+@pytest.mark.parametrize("alpha", [1.0, -1.0, 0.5 - 2.0j])
+def test_product_stage_edges(torch, m, n, k, alpha):
+    from paper_2601_04904_amd.solver import diag_gemm
+    rng = np.random.default_rng(m * 1000 + n * 50 + k)
+    for opA in (0, 1):
+        for opB in (0, 1):
+            A = crand(rng, *((k, m) if opA else (m, k)))
+            B = crand(rng, *((n, k) if opB else (k, n)))
+            C = crand(rng, m, n)
+            a, b = (A.conj().T if opA else A), (B.conj().T if opB else B)
+            ref = C + alpha * (a @ b)
+            bound = (k + 4) * EPS * 4 * (np.abs(C) + abs(alpha) * (np.abs(a) @ np.abs(b)))
+            dA, dB, dC = (torch.from_numpy(x).cuda() for x in (A, B, C))
+            for shape in (0, 1, 2):
+                out = diag_gemm(alpha, dA, opA, dB, opB, beta=1.0, Cin=dC, shape=shape).cpu().numpy()
+                assert (np.abs(out - ref) <= bound).all(), (opA, opB, shape)
+
+
+def test_more_products_than_one_search(torch):
+    """130 instances: launches of more than 128 products and inverses."""
+    import oracle
+    from tests._util import rel_err
+    from paper_2601_04904_amd import solver as S
+    from paper_2601_04904_amd.synth import gen_problem
+    probs = [gen_problem(3, 4 + i % 3, i % 2, 0.3, 0.05, 7 * i) for i in range(130)]
+    dA = [S.DeviceBlocks.from_host(A) for A, _ in probs]
+    dB = [S.DeviceBlocks.from_host(B) for _, B in probs]
+    XR = [S.DeviceBlocks.empty(A.n, A.b, A.a) for A, _ in probs]
+    XL = [S.DeviceBlocks.empty(A.n, A.b, A.a) for A, _ in probs]
+    bs = S.BatchSolver([dict(n=A.n, b=A.b, a=A.a) for A, _ in probs])
+    bs.solve(dA, dB, XR, XL)
+    bs.sync()
+    for i, (A, B) in enumerate(probs):
+        R, L = oracle.solve_dense(A, B)
+        assert rel_err(XR[i].to_host(), R) < 1e-11, i
+        assert rel_err(XL[i].to_host(), L) < 1e-11, i
+    bs.destroy()
+
+
+@pytest.mark.parametrize("d", [3, 4, 5, 31, 48, 49, 63, 64, 65, 79, 111, 112, 113, 127, 128, 129, 145, 255, 256, 257,
+                               511, 512, 513, 1023])
+def test_inverse_shape_edges(torch, d):
+    from paper_2601_04904_amd.solver import diag_inverse
+    rng = np.random.default_rng(d)
+    count = 3 if d <= 300 else 1
+    M = crand(rng, count, d, d) / np.sqrt(d)
+    M[:, np.arange(d), np.arange(d)] = 0.0                     # no pivot on the diagonal
+    M[0] *= 10.0 ** rng.uniform(-3, 3, size=(d, 1))            # rows of different size
+    dst, bad = diag_inverse(torch.from_numpy(M).cuda())
+    assert bad == -1
+    got = dst.cpu().numpy()
+    for i in range(count):
+        ref = np.linalg.inv(M[i])
+        err = np.linalg.norm(got[i] - ref) / np.linalg.norm(ref)
+        assert err < 50 * EPS * np.sqrt(d) * np.linalg.cond(M[i]), (i, err)
+
+
+@pytest.mark.parametrize("d", [40, 100, 120, 200, 300])
+def test_inverse_reports_singular(torch, d):
+    """A zero column: reported for every kernel shape, the other matrices inverted."""
+    from paper_2601_04904_amd.solver import diag_inverse
+    rng = np.random.default_rng(d)
+    M = crand(rng, 3, d, d) + np.eye(d)
+    M[1][:, d // 2] = 0.0
+    M[1][d // 2, :] = 0.0
+    dst, bad = diag_inverse(torch.from_numpy(M).cuda())
+    assert bad == 1
+    got = dst.cpu().numpy()
+    for i in (0, 2):
+        ref = np.linalg.inv(M[i])
+        assert np.linalg.norm(got[i] - ref) / np.linalg.norm(ref) < 1e-10
