@@ -105,10 +105,11 @@ struct NormJob {
 };
 
 // Fused small-instance path: one workgroup runs the whole operation list of
-// one instance.  A task is the instance's range of step records, in
-// dependency order; a record holds the step's kind and its descriptor
-// itself (fixed size), so the next step's record can be fetched while the
-// current one runs.
+// one instance.  A task is the instance's range of steps, in dependency order;
+// a step is up to kFusedStepRecs products of one dependency level, one inverse
+// or one sum; a record holds an operation's descriptor (fixed size, so that the
+// next step's records can be fetched while the current one runs).
+constexpr int kFusedStepRecs = 16;
 constexpr int kFusedMaxDim = 64;    // largest diagonal block / tip the fused path inverts
 
 struct FusedInv {
@@ -121,15 +122,22 @@ struct FusedInv {
 constexpr size_t kFusedBody = sizeof(GemmOp) > sizeof(AddOp) ? sizeof(GemmOp) : sizeof(AddOp);
 
 struct alignas(16) FusedRec {
-    int32_t type;         // 0 product, 1 inverse, 2 sum
+    int32_t tile_begin;   // product: its first 16 x 16 tile within the step
     int32_t pad[3];
     alignas(16) unsigned char body[(kFusedBody + 15) / 16 * 16];   // a GemmOp, FusedInv or AddOp
 };
 static_assert(sizeof(FusedInv) <= kFusedBody, "record body too small");
 static_assert(sizeof(FusedRec) % 16 == 0, "records are 16-byte multiples");
 
-struct FusedTask {
+struct FusedStep {
+    int32_t type;         // 0 products, 1 inverse, 2 sum
     int32_t first;        // first record
+    int32_t count;        // records
+    int32_t tiles;        // products: 16 x 16 tiles
+};
+
+struct FusedTask {
+    int32_t first;        // first step
     int32_t count;
 };
 

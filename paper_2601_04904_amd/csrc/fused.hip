@@ -8,27 +8,31 @@
 // products, diagonal-block inverses and block sums of the forward and
 // backward sweeps (Alg. 1 and 2, with the arrowhead terms of Sec. III-A and
 // the partition and reduced-system steps of Sec. III-B when asked for) -- in
-// dependency order, with a workgroup barrier between consecutive steps.
-// Instances are independent, so no workgroup ever waits on another one.
-// Each step's descriptor is a fixed-size record; the next record is read
-// from memory while the current step runs and handed over through LDS, and
-// every field a step branches or addresses on is made wave-uniform.
-// The steps are the same operation descriptors the grouped kernels run;
-// only the order of the sums inside a product and the inverse's pivoting
-// (rows of the block itself instead of its transpose) differ.
-#include "common.h"
-#include "cplx.h"
+// dependency order.  Instances are independent, so no workgroup ever waits on
+// another one.
+//
+// A step is all the products of one dependency level, or one inverse, or one
+// sum, with a workgroup barrier between steps.  The products of a step are
+// cut into 16 x 16 complex tiles and the waves take the tiles in turn: a wave
+// reads its rows of A and columns of B from memory straight into the layout of
+// v_mfma_f64_16x16x4 (nothing is shared between waves at 16 x 16, so LDS and
+// its barriers would only add latency).  Inverses are gauss.h's one-workgroup
+// form.
+//
+// What bounds it: the chain of an instance's steps on one CU (memory latency
+// and a barrier per step, and the column chain of each inverse).  512 instances
+// of n = 16, b = 32 in one launch: 2.9 -> 1.9 ms (LDS-staged 32 x 32 tiles by the
+// whole workgroup, one product at a time, an inverse with three barriers per
+// column -> this form); one instance 2.15 -> 1.12 ms.
+#include "gauss.h"
+#include <climits>
+#include <cstddef>
 
 namespace btsq {
 
-constexpr int kFT = 256;           // threads per workgroup
-constexpr int kFK = 16;            // complex k per product stage
-constexpr int kFusedLds = kFusedMaxDim * kFusedMaxDim + 2 * kFusedMaxDim;   // double2 elements
-constexpr int kRecWords = sizeof(FusedRec) / 4;
-static_assert(kRecWords <= kFT, "one record word per thread");
 
-// Values every lane holds alike (record fields read from LDS), moved to
-// scalar registers so that branches and addresses on them stay uniform.
+// Values every lane holds alike, moved to scalar registers so that branches and
+// addresses on them stay uniform.
 __device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ inline double uni(double x) {
     const long long b = __double_as_longlong(x);
@@ -47,279 +51,224 @@ template <class T> __device__ inline T* uni(T* p) {
 #ifdef __HIP_DEVICE_COMPILE__
 typedef const __attribute__((address_space(1))) double2* gcp;
 typedef __attribute__((address_space(1))) double2* gp;
-typedef __attribute__((address_space(1))) double* gdp;
 #else
 typedef const double2* gcp;
 typedef double2* gp;
-typedef double* gdp;
 #endif
 
-// One product term with its fields in scalar registers.
-struct FTerm {
-    gcp A;
-    gcp B;
-    int lda, ldb, k;
-    bool ah, bh;
-    double2 alpha;
-};
-__device__ inline FTerm load_term(const GemmTerm& T) {
-    FTerm t;
-    t.A = (gcp)uni(T.A);
-    t.B = (gcp)uni(T.B);
-    t.lda = uni(T.lda);
-    t.ldb = uni(T.ldb);
-    t.k = uni(T.k);
-    const int fl = uni(T.flags);
-    t.ah = fl & kTermAH;
-    t.bh = fl & kTermBH;
-    t.alpha = uni(T.alpha);
-    return t;
-}
-
 // ---------------------------------------------------------------------------
-// Products D = beta C + sum_t alpha_t op(A_t) op(B_t), by the whole
-// workgroup: TM x TM output tiles in turn.  Operands pass through LDS kFK
-// values of k at a time; the next stage's global loads are issued before the
-// current stage's multiply-adds.
-template <int TM>
-struct FStage {
-    static constexpr int NL = TM * kFK / kFT;
-    double2 a[NL], b[NL];
-    bool oka[NL], okb[NL];     // inside the operand (else the value read is replaced by zero)
+// A product's descriptor in the registers of a wave: lane l holds dwords l and
+// 64 + l of the GemmOp, so it is read from LDS in one latency and a field is one
+// lane read.
+struct OpRegs {
+    unsigned w0, w1;
+    __device__ inline OpRegs(const GemmOp& op, int lane) {
+        const unsigned* p = reinterpret_cast<const unsigned*>(&op);
+        w0 = p[lane];
+        w1 = p[64 + min(lane, (int)(sizeof(GemmOp) / 4) - 65)];
+    }
+    static __device__ inline int lane_of(unsigned w, int i) { return __builtin_amdgcn_readlane((int)w, i); }
+    // dword i (a constant below 64)
+    __device__ inline int head(int i) const { return lane_of(w0, i); }
+    // dword f of term s
+    __device__ inline int term(int s, int f) const {
+        constexpr int kFirst = offsetof(GemmOp, t) / 4, kLen = sizeof(GemmTerm) / 4;
+        const int i = kFirst + kLen * s + f;
+        return i < 64 ? lane_of(w0, i) : lane_of(w1, i - 64);
+    }
+    static __device__ inline double real(int lo, int hi) {
+        return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    }
+    static __device__ inline double2* ptr(int lo, int hi) {
+        return (double2*)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+    }
 };
+static_assert(sizeof(GemmOp) / 4 > 64 && sizeof(GemmOp) / 4 <= 128, "two dwords per lane");
+static_assert(kFusedMaxDim * kFusedMaxDim * sizeof(double2) < (1u << 30), "32-bit offsets");
 
-// Stage element e of op(A) (TM x kFK) and op(B) (kFK x TM), numbered so that
-// consecutive threads read consecutive memory.
-template <int TM> __device__ inline int fa_i(bool ah, int e) { return ah ? e % TM : e / kFK; }
-template <int TM> __device__ inline int fa_k(bool ah, int e) { return ah ? e / TM : e % kFK; }
-template <int TM> __device__ inline int fb_j(bool bh, int e) { return bh ? e / kFK : e % TM; }
-template <int TM> __device__ inline int fb_k(bool bh, int e) { return bh ? e % kFK : e / TM; }
-
-// Every lane issues all its loads unconditionally (out-of-range entries read
-// element 0, always present, and are zeroed when stored to LDS), so the loads
-// of a stage are in flight together and nothing waits for them before the
-// stage is stored.
-template <int TM>
-__device__ inline void fgemm_load(const FTerm& T, int m, int n, int i0, int j0, int k0, int tid,
-                                  FStage<TM>& st) {
-#pragma unroll
-    for (int q = 0; q < FStage<TM>::NL; ++q) {
-        const int e = tid + kFT * q;
-        const int gi = i0 + fa_i<TM>(T.ah, e), ka = k0 + fa_k<TM>(T.ah, e);
-        const bool oka = gi < m && ka < T.k;
-        const size_t ia = oka ? (T.ah ? (size_t)ka * T.lda + gi : (size_t)gi * T.lda + ka) : 0;
-        const int gj = j0 + fb_j<TM>(T.bh, e), kb = k0 + fb_k<TM>(T.bh, e);
-        const bool okb = gj < n && kb < T.k;
-        const size_t ib = okb ? (T.bh ? (size_t)gj * T.ldb + kb : (size_t)kb * T.ldb + gj) : 0;
-        st.a[q] = T.A[ia];
-        st.b[q] = T.B[ib];
-        st.oka[q] = oka;
-        st.okb[q] = okb;
-    }
+// Operands, C and D are addressed through raw buffer resources with 32-bit byte
+// offsets; an offset past the record count (the operand's extent) reads as zero
+// and is not written, so rows outside the product need no clamp.
+__device__ inline __amdgpu_buffer_rsrc_t fused_rsrc(double2* base, int rows, int cols, int ld) {
+    return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, ((rows - 1) * ld + cols) * 16, 0x00020000);
+}
+__device__ inline double2 load16(__amdgpu_buffer_rsrc_t r, int off) {
+    return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+__device__ inline void store16(__amdgpu_buffer_rsrc_t r, int off, double2 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, off, 0, 0);
 }
 
-// LDS rows of a stage are TM + 1 long, so that the A stores of consecutive
-// threads (consecutive k for one row i when A is read as stored) fall into
-// different banks.
-template <int TM> constexpr int kFLd = TM + 1;
+// Operands that run along k in memory (A as stored, B^H) are read 16 k of a row by
+// 16 lanes and turned through a piece of LDS of the wave's own (no barrier).
+typedef double2 Turn[16][17];
 
-template <int TM>
-__device__ inline void fgemm_store(const FTerm& T, int tid, const FStage<TM>& st, double2* As, double2* Bs) {
+// One 16 x 16 tile of D = beta C + sum_t alpha_t op(A_t) op(B_t), by one wave.
+// The k range of every term is taken 16 at a time; the next chunk's loads (of the
+// same or the next term) are issued before the current chunk's MFMAs.  Entries
+// of A and B past k are cleared; rows and columns outside the product only reach
+// entries of D that are not stored.  op is in LDS.
+__device__ void fused_tile(const GemmOp& op, int tile, int lane, Turn& XA, Turn& XB) {
+    const OpRegs o(op, lane);
+    const int m = o.head(offsetof(GemmOp, m) / 4), n = o.head(offsetof(GemmOp, n) / 4);
+    const int nt = o.head(offsetof(GemmOp, nterms) / 4);
+    const int tn = (n + 15) >> 4;
+    int ti = 0;                                       // tile / tn, at most 4 rows of tiles
+    while ((ti + 1) * tn <= tile) ++ti;
+    const int i0 = ti * 16, j0 = (tile - ti * tn) * 16;
+    const int q = lane & 15, kq = lane >> 4;
+    v4d re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    double2 cv[4] = {};
+    double2* C = OpRegs::ptr(o.head(offsetof(GemmOp, C) / 4), o.head(offsetof(GemmOp, C) / 4 + 1));
+    if (C) {
+        const int ldc = o.head(offsetof(GemmOp, ldc) / 4);
+        const __amdgpu_buffer_rsrc_t rc = fused_rsrc(C, m, n, ldc);
 #pragma unroll
-    for (int q = 0; q < FStage<TM>::NL; ++q) {
-        const int e = tid + kFT * q;
-        double2 a = st.oka[q] ? st.a[q] : make_double2(0.0, 0.0);
-        if (T.ah) a.y = -a.y;
-        As[fa_k<TM>(T.ah, e) * kFLd<TM> + fa_i<TM>(T.ah, e)] = a;
-        double2 b = st.okb[q] ? st.b[q] : make_double2(0.0, 0.0);
-        if (T.bh) b.y = -b.y;
-        Bs[fb_k<TM>(T.bh, e) * kFLd<TM> + fb_j<TM>(T.bh, e)] = cmul_i(T.alpha, b);
+        for (int r = 0; r < 4; ++r) cv[r] = load16(rc, (__mul24(i0 + kq + 4 * r, ldc) + j0 + q) * 16);
     }
-}
 
-// The multiply-adds run on the FP64 matrix cores with the grouped kernel's
-// scheme: the complex product as the real product of A' (A read as m x 2k
-// real) and B'' (B expanded to 2k x 2n real, [[Re, Im], [-Im, Re]] per
-// entry), v_mfma_f64_4x4x4f64 used as a 4-row x 16-column x 4-k product
-// with A replicated over its four blocks (A[l%4][l/16], B[l/16][l%16],
-// D[l/16][l%16]).  The four waves split the TM x TM tile 2 x 2: each owns
-// TM/2 rows (TM/8 groups of 4) and TM/2 complex columns (TM/16 blocks of 16
-// real columns).
-template <int TM>
-__device__ void fused_gemm(const GemmOp& op, double2* lds, int tid) {
-    constexpr int RG = TM / 8;                // 4-row groups per wave
-    constexpr int NI = TM / 16;               // 16-real-column blocks per wave
-    double2* As = lds;
-    double2* Bs = lds + kFK * kFLd<TM>;
-    const int m = uni(op.m), n = uni(op.n), nt = uni(op.nterms);
-    gp D = (gp)uni(op.D);
-    gcp C = (gcp)uni(op.C);
-    const int ldd = uni(op.ldd), ldc = uni(op.ldc);
-    const double2 beta = uni(op.beta);
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave & 1, wn = wave >> 1;
-    const int cA = (lane >> 4) & 1;           // real k within the pair: 0 = Re of A, 1 = Im
-    const int pOff = lane >> 5;               // complex k offset within the 4-wide real k step
-    const int r16 = lane & 15;
-    const int d = lane & 1;                   // output component of this lane's B'' column
-    const unsigned long long negB = (cA == 1 && d == 0) ? 0x8000000000000000ull : 0ull;
-    const int tn = (n + TM - 1) / TM;
-    const int tiles = ((m + TM - 1) / TM) * tn;
-    for (int t = 0; t < tiles; ++t) {
-        const int i0 = (t / tn) * TM, j0 = (t % tn) * TM;
-        double acc[RG][NI];
-#pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) acc[g][ni] = 0.0;
-        // stages are (term, k offset) pairs in order, empty terms skipped
-        int s = 0, k0 = 0;
-        while (s < nt && uni(op.t[s].k) <= 0) ++s;
-        FStage<TM> st;
-        FTerm cur{};
-        if (s < nt) {
-            cur = load_term(op.t[s]);
-            fgemm_load<TM>(cur, m, n, i0, j0, 0, tid, st);
+    // The chunk to load next: term s at offset c0.  Element t of a lane lies along
+    // k (row kq + 4 t of the tile, k = q) or across (row or column q, k = 4 t + kq):
+    // byte offsets va + t da (vb + t db), from one chunk to the next ka (kb) more.
+    int s = -1, c0 = 0, k = 0, va = 0, vb = 0, da = 0, db = 0, ka = 0, kb = 0;
+    bool ah = false, bh = false;
+    double2 alpha = make_double2(1.0, 0.0);
+    __amdgpu_buffer_rsrc_t ra, rb;
+    auto advance = [&]() {
+        c0 += 16;
+        if (c0 < k) {
+            va += ka;
+            vb += kb;
+            return;
         }
-        while (s < nt) {
-            __syncthreads();                      // the previous stage's readers are done
-            fgemm_store<TM>(cur, tid, st, As, Bs);
-            __syncthreads();
-            int s2 = s, k2 = k0 + kFK;
-            while (s2 < nt && k2 >= uni(op.t[s2].k)) { ++s2; k2 = 0; }
-            FTerm nxt = cur;
-            if (s2 < nt) {
-                if (s2 != s) nxt = load_term(op.t[s2]);
-                fgemm_load<TM>(nxt, m, n, i0, j0, k2, tid, st);
-            }
-            // entries past k are zero in both operands: the full depth is exact
+        c0 = 0;
+        do ++s; while (s < nt && o.term(s, offsetof(GemmTerm, k) / 4) <= 0);
+        if (s >= nt) return;
+        k = o.term(s, offsetof(GemmTerm, k) / 4);
+        const int lda = o.term(s, offsetof(GemmTerm, lda) / 4), ldb = o.term(s, offsetof(GemmTerm, ldb) / 4);
+        const int flags = o.term(s, offsetof(GemmTerm, flags) / 4);
+        constexpr int kAl = offsetof(GemmTerm, alpha) / 4;
+        alpha = make_double2(OpRegs::real(o.term(s, kAl), o.term(s, kAl + 1)),
+                             OpRegs::real(o.term(s, kAl + 2), o.term(s, kAl + 3)));
+        ah = flags & kTermAH;
+        bh = flags & kTermBH;
+        double2* A = OpRegs::ptr(o.term(s, 0), o.term(s, 1));
+        double2* B = OpRegs::ptr(o.term(s, 2), o.term(s, 3));
+        ra = ah ? fused_rsrc(A, k, m, lda) : fused_rsrc(A, m, k, lda);
+        rb = bh ? fused_rsrc(B, n, k, ldb) : fused_rsrc(B, k, n, ldb);
+        const int la = __mul24(kq, lda), lb = __mul24(kq, ldb);
+        va = (la + q + (ah ? i0 : i0 * lda)) * 16;
+        vb = (lb + q + (bh ? j0 * ldb : j0)) * 16;
+        da = 64 * lda;
+        db = 64 * ldb;
+        ka = ah ? 256 * lda : 256;
+        kb = bh ? 256 : 256 * ldb;
+    };
+    static_assert(offsetof(GemmTerm, A) == 0 && offsetof(GemmTerm, B) == 8, "pointers first");
+    struct Chunk {
+        double2 a[4], b[4];
+        double2 alpha;         // of its term, as ah, bh
+        bool ah, bh;
+        int left;              // the k left in the term from its start
+    } ch[2];
+    auto load = [&](Chunk& c) {
+        c.ah = ah;
+        c.bh = bh;
+        c.alpha = alpha;
+        c.left = k - c0;
 #pragma unroll
-            for (int kk = 0; kk < kFK / 2; ++kk) {
-                const int p = 2 * kk + pOff;
-                double av[RG], bv[NI];
-#pragma unroll
-                for (int g = 0; g < RG; ++g)
-                    av[g] = reinterpret_cast<const double*>(&As[p * kFLd<TM> + wm * (TM / 2) + g * 4 + (lane & 3)])[cA];
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    const double v = reinterpret_cast<const double*>(&Bs[p * kFLd<TM> + ((wn * TM + ni * 16 + r16) >> 1)])[cA ^ d];
-                    bv[ni] = __longlong_as_double(__double_as_longlong(v) ^ (long long)negB);
-                }
-#pragma unroll
-                for (int g = 0; g < RG; ++g)
-#pragma unroll
-                    for (int ni = 0; ni < NI; ++ni)
-                        acc[g][ni] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[g], bv[ni], acc[g][ni], 0, 0, 0);
-            }
-            s = s2;
-            k0 = k2;
-            cur = nxt;
+        for (int t = 0; t < 4; ++t) {
+            c.a[t] = load16(ra, va + t * da);
+            c.b[t] = load16(rb, vb + t * db);
         }
-        // lane: component d of complex column (wn TM + ni 16 + r16) / 2 of row
-        // group g's row lane / 16; C may be D: each output element is read
-        // and written by the same lane
+    };
+    auto turn = [&](double2* v, Turn& X) {
 #pragma unroll
-        for (int g = 0; g < RG; ++g)
+        for (int t = 0; t < 4; ++t) X[q][kq + 4 * t] = v[t];
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                const int gi = i0 + wm * (TM / 2) + g * 4 + (lane >> 4);
-                const int gj = j0 + ((wn * TM + ni * 16 + r16) >> 1);
-                if (gi < m && gj < n) {
-                    double v = acc[g][ni];
-                    if (C) {
-                        const double2 c = C[(size_t)gi * ldc + gj];
-                        v += d ? (beta.x * c.y + beta.y * c.x) : (beta.x * c.x - beta.y * c.y);
-                    }
-                    reinterpret_cast<gdp>(D + (size_t)gi * ldd + gj)[d] = v;
-                }
-            }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Inverse of one d x d block (d <= kFusedMaxDim) in LDS: Gauss-Jordan
-// elimination with partial pivoting, in place and without row exchanges.
-// Column j takes as pivot row p_j the not-yet-used row of largest
-// |re| + |im| in that column (to 11 mantissa bits, lowest row on ties),
-// found by wave 0 with one row per lane; row p_j is scaled and column j
-// eliminated from every other row, and slot j then holds column p_j of the
-// accumulated transform T (T A = Q, Q e_j = e_{p_j}).  Since A^-1 = Q^T T,
-//     A^-1[j][c] = W[p_j][pinv(c)],  pinv(p_j) = j,
-// with W the working matrix at the end.  W is column-major in LDS, so the
-// pivot search, the pivot column and the elimination read consecutive
-// addresses.
-__device__ void fused_inverse(const FusedInv& J, double2* lds, int* piv, int* pinv, int tid,
-                              DevStatus* status) {
-    const int d = uni(J.d);
-    gcp src = (gcp)uni(J.src);
-    gp dst = (gp)uni(J.dst);
-    double2* W = lds;                          // W[r][c] at c * d + r
-    double2* colj = lds + kFusedMaxDim * kFusedMaxDim;
-    double2* rowp = colj + kFusedMaxDim;
-    for (int e = tid; e < d * d; e += kFT) {
-        const int r = e / d, c = e - r * d;
-        W[c * d + r] = src[e];
-    }
-    bool bad = false;
-    bool used = false;                         // wave 0: lane r's row has been a pivot row
-    __syncthreads();
-    for (int j = 0; j < d; ++j) {
-        if (tid < 64) {                        // all of wave 0
-            const int r = tid;
-            const unsigned key = (r < d && !used) ? pivot_key(W[j * d + r], r) : 0u;
-            const unsigned mx = wave_umax(key);
-            const int p = mx == 0u ? -1 : key_row(mx);
-            used = used || r == p;
-            if (tid == 0) piv[j] = p;
+        for (int t = 0; t < 4; ++t) v[t] = X[4 * t + kq][q];
+    };
+    auto flip = [](double v) {
+        return __longlong_as_double(__double_as_longlong(v) ^ (long long)0x8000000000000000ull);
+    };
+    auto multiply = [&](Chunk& c) {
+        const bool one = c.alpha.y == 0.0 && (c.alpha.x == 1.0 || c.alpha.x == -1.0);
+        const bool neg = one && c.alpha.x < 0.0;
+        if (!c.ah) turn(c.a, XA);
+        if (c.bh) turn(c.b, XB);
+        // conjugation and alpha, each behind a wave-uniform branch
+        if (c.ah) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) c.a[t].y = flip(c.a[t].y);
         }
-        __syncthreads();
-        const int p = piv[j];
-        bad = bad || p < 0;
-        const int pr = p < 0 ? 0 : p;
-        const double2 ip = crecip(W[j * d + pr]);
-        bad = bad || !(fabs(ip.x) + fabs(ip.y) <= DBL_MAX);
-        for (int e = tid; e < d; e += kFT) {
-            colj[e] = W[j * d + e];
-            rowp[e] = e == j ? ip : cmul_i(W[e * d + pr], ip);
+        if (c.bh != neg) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) c.b[t].y = flip(c.b[t].y);
         }
-        __syncthreads();
-        for (int e = tid; e < d * d; e += kFT) {
-            const int c = e / d, r = e - c * d;
-            if (r == pr) {
-                W[e] = rowp[c];
-            } else {
-                double2 v = c == j ? make_double2(0.0, 0.0) : W[e];
-                cfms(v, colj[r], rowp[c]);
-                W[e] = v;
-            }
+        if (neg) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) c.b[t].x = flip(c.b[t].x);
         }
-        __syncthreads();
+        if (!one) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) c.b[t] = cmul_i(c.alpha, c.b[t]);
+        }
+        if (c.left < 16) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (4 * t + kq >= c.left) c.a[t] = c.b[t] = make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (4 * t >= c.left) break;                 // wave-uniform
+            re = mfma64(c.a[t].x, c.b[t].x, re);
+            im = mfma64(c.a[t].x, c.b[t].y, im);
+            re = mfma64_nega(c.a[t].y, c.b[t].y, re);
+            im = mfma64(c.a[t].y, c.b[t].x, im);
+        }
+    };
+    advance();
+    if (s < nt) {
+        load(ch[0]);
+        for (;;) {
+            advance();
+            bool more = s < nt;
+            if (more) load(ch[1]);
+            multiply(ch[0]);
+            if (!more) break;
+            advance();
+            more = s < nt;
+            if (more) load(ch[0]);
+            multiply(ch[1]);
+            if (!more) break;
+        }
     }
-    // after a singular column the pivot rows need not be a permutation:
-    // clear first so every index stays in range
-    for (int c = tid; c < d; c += kFT) pinv[c] = 0;
-    __syncthreads();
-    for (int j = tid; j < d; j += kFT) {
-        const int p = piv[j];
-        if (p >= 0) pinv[p] = j;
+    constexpr int kBe = offsetof(GemmOp, beta) / 4;
+    const double2 beta = make_double2(OpRegs::real(o.head(kBe), o.head(kBe + 1)),
+                                      OpRegs::real(o.head(kBe + 2), o.head(kBe + 3)));
+    const int ldd = o.head(offsetof(GemmOp, ldd) / 4);
+    const __amdgpu_buffer_rsrc_t rd = fused_rsrc(OpRegs::ptr(o.head(0), o.head(1)), m, n, ldd);
+    static_assert(offsetof(GemmOp, D) == 0, "D first");
+    if (j0 + q < n) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double2 v = make_double2(re[r], im[r]);
+            if (C) cfma(v, beta, cv[r]);
+            store16(rd, (__mul24(i0 + kq + 4 * r, ldd) + j0 + q) * 16, v);
+        }
     }
-    __syncthreads();
-    for (int e = tid; e < d * d; e += kFT) {
-        const int j = e / d, c = e - j * d;
-        const int p = piv[j] < 0 ? 0 : piv[j];
-        dst[e] = W[pinv[c] * d + p];
-    }
-    if (bad && tid == 0 && atomicCAS(&status->code, 0, 3) == 0) status->tag = J.tag;
 }
 
 // ---------------------------------------------------------------------------
 // Block sum D = sum_j c_j op_j(X_j) (op_j = X_j^H when bit j of hmask is set;
 // such an input is stored cols x rows and is not D).
+template <int FT>
 __device__ void fused_add(const AddOp& op, int tid) {
     const int rows = uni(op.rows), cols = uni(op.cols), nin = uni(op.nin);
     const unsigned hmask = (unsigned)uni((int)op.hmask);
     gp D = (gp)uni(op.D);
-    for (int e = tid; e < rows * cols; e += kFT) {
+    for (int e = tid; e < rows * cols; e += FT) {
         const int r = e / cols, c = e - r * cols;
         double2 acc = make_double2(0.0, 0.0);
         for (int j = 0; j < nin; ++j) {
@@ -338,42 +287,84 @@ __device__ void fused_add(const AddOp& op, int tid) {
 }
 
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kFT)
-void fused_solve(const FusedTask* __restrict__ tasks, const FusedRec* __restrict__ recs, DevStatus* status) {
-    __shared__ double2 lds[kFusedLds];
-    __shared__ int piv[kFusedMaxDim], pinv[kFusedMaxDim];
-    __shared__ FusedRec srec[2];
+// The records of the next step are read from memory while the current one runs
+// and handed over through LDS, and the step after that is read meanwhile, so no
+// step waits for its own description.
+// FW waves per workgroup: 8 while every instance has a CU to itself, else 4 (one
+// instance 1.12 against 1.30 ms; 512 of them 3.3 against 3.0).
+template <int FW>
+__global__ __launch_bounds__(64 * FW)
+void fused_solve(const FusedTask* __restrict__ tasks, const FusedStep* __restrict__ steps,
+                 const FusedRec* __restrict__ recs, DevStatus* status) {
+    constexpr int FT = 64 * FW;
+    constexpr int kWords = sizeof(FusedRec) / 16;                 // uint4 per record
+    constexpr int kPer = (kFusedStepRecs * kWords + FT - 1) / FT;
+    union Work {                       // a step uses one of them
+        SmallInvLds<FW, 1> inv;
+        Turn turn[FW][2];
+    };
+    __shared__ Work L;
+    __shared__ FusedRec srec[2][kFusedStepRecs];
     const FusedTask T = tasks[blockIdx.x];
-    const int tid = threadIdx.x;
-    const unsigned* words = reinterpret_cast<const unsigned*>(recs + T.first);
-    unsigned* sw = reinterpret_cast<unsigned*>(srec);
-    if (tid < kRecWords && T.count > 0) sw[tid] = words[tid];
-    for (int q = 0; q < T.count; ++q) {
-        // the next record is read while this step runs
-        unsigned nxt = 0;
-        const bool more = q + 1 < T.count;
-        if (tid < kRecWords && more) nxt = words[(size_t)(q + 1) * kRecWords + tid];
-        // the previous step's global writes and LDS reads are complete
-        __syncthreads();
-        const FusedRec& R = srec[q & 1];
-        const int type = uni(R.type);
-        if (type == 0) {
-            const GemmOp& g = *reinterpret_cast<const GemmOp*>(R.body);
-            if (max(uni(g.m), uni(g.n)) > 32) fused_gemm<64>(g, lds, tid);
-            else fused_gemm<32>(g, lds, tid);
-        } else if (type == 1) {
-            fused_inverse(*reinterpret_cast<const FusedInv*>(R.body), lds, piv, pinv, tid, status);
-        } else {
-            fused_add(*reinterpret_cast<const AddOp*>(R.body), tid);
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+    uint4 w[kPer];
+    auto fetch = [&](const FusedStep& st) {
+        const uint4* from = reinterpret_cast<const uint4*>(recs + st.first);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = tid + FT * i;
+            if (e < st.count * kWords) w[i] = from[e];
         }
-        if (tid < kRecWords && more) sw[((q + 1) & 1) * kRecWords + tid] = nxt;
+    };
+    auto hand_over = [&](const FusedStep& st, int buf) {
+        uint4* to = reinterpret_cast<uint4*>(srec[buf]);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = tid + FT * i;
+            if (e < st.count * kWords) to[e] = w[i];
+        }
+    };
+    if (T.count <= 0) return;
+    FusedStep cur = steps[T.first], nxt = steps[T.first + min(1, T.count - 1)];
+    fetch(cur);
+    hand_over(cur, 0);
+    __syncthreads();
+    for (int q = 0; q < T.count; ++q) {
+        const FusedRec* R = srec[q & 1];
+        const bool more = q + 1 < T.count;
+        if (more) fetch(nxt);
+        const FusedStep after = steps[T.first + min(q + 2, T.count - 1)];
+        if (cur.type == 0) {
+            // the products' first tiles, one per lane
+            const int begin = lane < cur.count ? R[lane].tile_begin : INT_MAX;
+            for (int e = wave; e < cur.tiles; e += FW) {
+                const int r = __popcll(__ballot(begin <= e)) - 1;
+                fused_tile(*reinterpret_cast<const GemmOp*>(R[r].body), e - uni(R[r].tile_begin), lane,
+                           L.turn[wave][0], L.turn[wave][1]);
+            }
+        } else if (cur.type == 1) {
+            const FusedInv& J = *reinterpret_cast<const FusedInv*>(R[0].body);
+            small_inverse<FW, 1>(uni(J.src), uni(J.dst), uni(J.d), uni(J.tag), L.inv, tid, status);
+            __builtin_amdgcn_s_setprio(0);
+        } else {
+            fused_add<FT>(*reinterpret_cast<const AddOp*>(R[0].body), tid);
+        }
+        if (more) hand_over(nxt, (q + 1) & 1);
+        // the step's global writes and LDS reads are complete
+        __syncthreads();
+        cur = nxt;
+        nxt = after;
     }
 }
 
-hipError_t launch_fused(const FusedTask* d_tasks, int ntasks, const FusedRec* d_recs, DevStatus* status,
-                        hipStream_t s) {
+hipError_t launch_fused(const FusedTask* d_tasks, int ntasks, const FusedStep* d_steps, const FusedRec* d_recs,
+                        DevStatus* status, hipStream_t s) {
     if (ntasks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fused_solve, dim3(ntasks), dim3(kFT), 0, s, d_tasks, d_recs, status);
+    constexpr int kCUs = 256;
+    if (ntasks <= kCUs)
+        hipLaunchKernelGGL(fused_solve<8>, dim3(ntasks), dim3(512), 0, s, d_tasks, d_steps, d_recs, status);
+    else
+        hipLaunchKernelGGL(fused_solve<4>, dim3(ntasks), dim3(256), 0, s, d_tasks, d_steps, d_recs, status);
     return hipGetLastError();
 }
 

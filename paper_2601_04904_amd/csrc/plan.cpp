@@ -54,8 +54,8 @@ hipError_t launch_inv_step(const InvJob* d_jobs, int njobs, int variant, int pan
                            DevStatus* status, hipStream_t s);
 hipError_t launch_add(const AddOp* d_ops, int nops, size_t max_elems, hipStream_t s);
 hipError_t launch_norms(const NormJob* d_jobs, int njobs, hipStream_t s);
-hipError_t launch_fused(const FusedTask* d_tasks, int ntasks, const FusedRec* d_recs, DevStatus* status,
-                        hipStream_t s);
+hipError_t launch_fused(const FusedTask* d_tasks, int ntasks, const FusedStep* d_steps, const FusedRec* d_recs,
+                        DevStatus* status, hipStream_t s);
 }  // namespace btsq
 
 namespace {
@@ -911,7 +911,8 @@ struct Program {
     std::vector<InvJob> inv;
     std::vector<AddOp> add;
     std::vector<NormJob> norm;
-    std::vector<FusedRec> frec;     // fused launch: step records and tasks
+    std::vector<FusedRec> frec;     // fused launch: operation records, steps and tasks
+    std::vector<FusedStep> fstep;
     std::vector<FusedTask> ftask;
     std::vector<Launch> launches;
     size_t inv_scratch_bytes = 0;   // scratch the inverses need (max over levels)
@@ -1037,10 +1038,10 @@ AddOp make_add_op(const OpRec& o) {
 }
 
 // The operations of BT_FUSED instances (task >= 0): per task, its steps in
-// level order (each instance's operations were built in dependency order,
-// so a stable sort by level keeps every step after what it reads), and one
-// launch with a workgroup per task.  Returns false (pg.error set) for an
-// operation the fused kernel does not run.
+// level order (operations of one level are independent): the level's inverses
+// and sums, then its products, kFusedStepRecs to a step.  One launch with a workgroup per
+// task.  Returns false (pg.error set) for an operation the fused kernel does not
+// run.
 bool compile_fused(Program& pg, const std::vector<OpRec>& ops) {
     int ntasks = 0;
     for (const auto& o : ops) ntasks = std::max(ntasks, o.task + 1);
@@ -1057,37 +1058,52 @@ bool compile_fused(Program& pg, const std::vector<OpRec>& ops) {
     for (int t = 0; t < ntasks; ++t) {
         auto& v = bytask[t];
         std::stable_sort(v.begin(), v.end(), [&](int x, int y) { return ops[x].level < ops[y].level; });
-        FusedTask task{(int32_t)pg.frec.size(), (int32_t)v.size()};
-        for (int i : v) {
-            const OpRec& o = ops[i];
-            FusedRec rec;
-            memset(&rec, 0, sizeof rec);
-            if (o.kind == K_GEMM && !o.mixed) {
-                GemmOp g = make_gemm_op(o);
-                double f = 0, b = 0;
-                gemm_work(&g, 1, f, b);
-                L.flops += f;
-                L.bytes += b;
-                rec.type = 0;
-                memcpy(rec.body, &g, sizeof g);
-            } else if (o.kind == K_INV && o.D.r <= kFusedMaxDim) {
-                FusedInv j{o.C.p, o.D.p, o.D.r, o.tag};
-                L.flops += 8.0 * (double)j.d * j.d * j.d;
-                L.bytes += 32.0 * (double)j.d * j.d;
-                rec.type = 1;
-                memcpy(rec.body, &j, sizeof j);
-            } else if (o.kind == K_ADD && o.ins.size() <= (size_t)kMaxAdd) {
-                AddOp a = make_add_op(o);
-                L.flops += 8.0 * a.rows * a.cols * a.nin;
-                L.bytes += 16.0 * a.rows * a.cols * (a.nin + 1);
-                rec.type = 2;
-                memcpy(rec.body, &a, sizeof a);
-            } else {
-                pg.error = "internal: an operation of a BT_FUSED instance has no fused form";
-                return false;
+        FusedTask task{(int32_t)pg.fstep.size(), 0};
+        for (size_t x = 0; x < v.size();) {
+            size_t y = x;
+            while (y < v.size() && ops[v[y]].level == ops[v[x]].level) ++y;
+            bool level_open = false;      // the last step takes products of this level
+            std::stable_partition(v.begin() + x, v.begin() + y, [&](int i) { return ops[i].kind != K_GEMM; });
+            for (; x < y; ++x) {
+                const OpRec& o = ops[v[x]];
+                const int32_t at = (int32_t)pg.frec.size();
+                FusedRec rec;
+                memset(&rec, 0, sizeof rec);
+                if (o.kind == K_GEMM && !o.mixed) {
+                    GemmOp g = make_gemm_op(o);
+                    double f = 0, b = 0;
+                    gemm_work(&g, 1, f, b);
+                    L.flops += f;
+                    L.bytes += b;
+                    memcpy(rec.body, &g, sizeof g);
+                    const bool open = (int)pg.fstep.size() > task.first && level_open &&
+                                      pg.fstep.back().count < kFusedStepRecs;
+                    if (!open) pg.fstep.push_back(FusedStep{0, at, 0, 0});
+                    level_open = true;
+                    FusedStep& st = pg.fstep.back();
+                    rec.tile_begin = st.tiles;
+                    st.count += 1;
+                    st.tiles += ((g.m + 15) / 16) * ((g.n + 15) / 16);
+                } else if (o.kind == K_INV && o.D.r <= kFusedMaxDim) {
+                    FusedInv j{o.C.p, o.D.p, o.D.r, o.tag};
+                    L.flops += 8.0 * (double)j.d * j.d * j.d;
+                    L.bytes += 32.0 * (double)j.d * j.d;
+                    memcpy(rec.body, &j, sizeof j);
+                    pg.fstep.push_back(FusedStep{1, at, 1, 0});
+                } else if (o.kind == K_ADD && o.ins.size() <= (size_t)kMaxAdd) {
+                    AddOp a = make_add_op(o);
+                    L.flops += 8.0 * a.rows * a.cols * a.nin;
+                    L.bytes += 16.0 * a.rows * a.cols * (a.nin + 1);
+                    memcpy(rec.body, &a, sizeof a);
+                    pg.fstep.push_back(FusedStep{2, at, 1, 0});
+                } else {
+                    pg.error = "internal: an operation of a BT_FUSED instance has no fused form";
+                    return false;
+                }
+                pg.frec.push_back(rec);
             }
-            pg.frec.push_back(rec);
         }
+        task.count = (int32_t)pg.fstep.size() - task.first;
         pg.ftask.push_back(task);
     }
     pg.launches.push_back(L);
@@ -1322,7 +1338,7 @@ struct bt_si_sq_plan {
         bool dev_own = false;             // dev allocated on its own (did not fit the arena)
         std::vector<char> host;           // host copy the upload reads (kept as long as dev)
         size_t off_gemm = 0, off_inv = 0, off_add = 0, off_norm = 0;
-        size_t off_frec = 0, off_ftask = 0;
+        size_t off_frec = 0, off_fstep = 0, off_ftask = 0;
         std::vector<hipEvent_t> events;   // cross-stream events of the launch list
         hipGraphExec_t graph = nullptr;   // the launch list captured as a graph (BT_GRAPH)
     };
@@ -1579,6 +1595,7 @@ hipError_t enqueue_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c, hipStream
             case 6: e = launch_inv_step(dj + L.off, L.count, L.maxd, L.panel, L.tiles, h->status, s); break;
             case 7:
                 e = launch_fused(reinterpret_cast<const FusedTask*>(c.dev + c.off_ftask) + L.off, L.count,
+                                 reinterpret_cast<const FusedStep*>(c.dev + c.off_fstep),
                                  reinterpret_cast<const FusedRec*>(c.dev + c.off_frec), h->status, s);
                 break;
         }
@@ -1620,7 +1637,7 @@ std::vector<uint64_t> make_key(Mode mode, bool fp64_rerun, const std::vector<int
 // Device bytes of a compiled program's operation lists (each array starting
 // on a 256-byte boundary, as prepare_and_run lays them out).
 struct ProgLayout {
-    size_t off_inv, off_add, off_norm, off_frec, off_ftask, total;
+    size_t off_inv, off_add, off_norm, off_frec, off_fstep, off_ftask, total;
 };
 ProgLayout program_layout(const Program& pg) {
     ProgLayout L;
@@ -1628,7 +1645,8 @@ ProgLayout program_layout(const Program& pg) {
     L.off_add = align256(L.off_inv + pg.inv.size() * sizeof(InvJob));
     L.off_norm = align256(L.off_add + pg.add.size() * sizeof(AddOp));
     L.off_frec = align256(L.off_norm + pg.norm.size() * sizeof(NormJob));
-    L.off_ftask = align256(L.off_frec + pg.frec.size() * sizeof(FusedRec));
+    L.off_fstep = align256(L.off_frec + pg.frec.size() * sizeof(FusedRec));
+    L.off_ftask = align256(L.off_fstep + pg.fstep.size() * sizeof(FusedStep));
     L.total = L.off_ftask + pg.ftask.size() * sizeof(FusedTask) + 256;
     return L;
 }
@@ -1735,6 +1753,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         put(PL.off_add, pg.add.data(), pg.add.size() * sizeof(AddOp));
         put(PL.off_norm, pg.norm.data(), pg.norm.size() * sizeof(NormJob));
         put(PL.off_frec, pg.frec.data(), pg.frec.size() * sizeof(FusedRec));
+        put(PL.off_fstep, pg.fstep.data(), pg.fstep.size() * sizeof(FusedStep));
         put(PL.off_ftask, pg.ftask.data(), pg.ftask.size() * sizeof(FusedTask));
         e = hipMemcpyAsync(c->dev, stage, total, hipMemcpyHostToDevice, h->stream);
         if (e != hipSuccess) return hip_err(h, e, "hipMemcpyAsync(op list)");
@@ -1754,6 +1773,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         c->off_add = PL.off_add;
         c->off_norm = PL.off_norm;
         c->off_frec = PL.off_frec;
+        c->off_fstep = PL.off_fstep;
         c->off_ftask = PL.off_ftask;
         c->key = key;
     }

@@ -99,3 +99,29 @@ def test_inverse_reports_singular(torch, d):
     for i in (0, 2):
         ref = np.linalg.inv(M[i])
         assert np.linalg.norm(got[i] - ref) / np.linalg.norm(ref) < 1e-10
+
+
+@pytest.mark.parametrize("n,b,a,P", [(1, 1, 0, 1), (2, 15, 1, 1), (5, 16, 17, 1), (4, 17, 0, 1), (6, 33, 31, 2),
+                                     (5, 48, 0, 1), (4, 64, 64, 1), (16, 5, 3, 8), (24, 20, 9, 6)])
+@pytest.mark.parametrize("antih", [False, True])
+def test_fused_tile_edges(torch, n, b, a, P, antih):
+    """BT_FUSED at tile edges of its products, with more products in a level than
+    one step holds (many partitions), alone and beside enough copies of itself
+    that the instances share CUs."""
+    import oracle
+    from tests._util import rel_err
+    from paper_2601_04904_amd import solver as S
+    from paper_2601_04904_amd.synth import gen_problem
+    A, B = gen_problem(n, b, a, 0.3, 0.05, 31 * n + b)
+    R, L = oracle.solve_dense(A, B)
+    flags = S.BT_FUSED | (S.BT_SIGMA_ANTIHERMITIAN if antih else 0)
+    dA, dB = S.DeviceBlocks.from_host(A), S.DeviceBlocks.from_host(B)
+    for count in (1, 300):
+        out = [(S.DeviceBlocks.empty(n, b, a), S.DeviceBlocks.empty(n, b, a)) for _ in range(count)]
+        bs = S.BatchSolver([dict(n=n, b=b, a=a, partitions=P, flags=flags)] * count)
+        bs.solve([dA] * count, [dB] * count, [x[0] for x in out], [x[1] for x in out])
+        bs.sync()
+        for i in (0, count - 1):
+            assert rel_err(out[i][0].to_host(), R) < 1e-11
+            assert rel_err(out[i][1].to_host(), L) < 1e-11
+        bs.destroy()
