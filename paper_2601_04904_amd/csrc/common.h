@@ -22,8 +22,8 @@ constexpr int kTermAH = 1;
 constexpr int kTermBH = 2;
 
 // D = beta * C + sum_t alpha_t op(A_t) op(B_t), D and C m x n (C may alias D
-// or be null, then beta is ignored).  tile_begin: first tile of this product
-// in the launch (products of one launch are independent of each other).
+// or be null, then beta is ignored).  Products of one launch are independent of
+// each other.
 struct GemmOp {
     double2* D;
     const double2* C;
@@ -31,14 +31,16 @@ struct GemmOp {
     int32_t m, n;
     int32_t nterms;
     int32_t tiles_n;      // tiles along n
-    int32_t tile_begin;
     int32_t mixed;        // 1: products in complex64 (FP32 MFMA, FP32 accumulation)
     double2 beta;
     GemmTerm t[kMaxTerms];
 };
 
-// One diagonal-block inverse dst = src^-1 (d x d) by blocked Gauss-Jordan
-// elimination with partial pivoting inside the block.
+// Tile order of a product launch: workgroup b computes tile (entry & mask) of
+// product (entry >> kTileBits); kNoTile: nothing to do.
+constexpr int kTileBits = 11;
+constexpr uint32_t kNoTile = 0xffffffffu;
+
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  This maps dispatch index b of a grid of g workgroups to a logical
 // index so that each XCD receives one contiguous range of logical indices,
@@ -51,6 +53,8 @@ __device__ inline int xcd_remap(int b, int g) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
+// One diagonal-block inverse dst = src^-1 (d x d) by blocked Gauss-Jordan
+// elimination with partial pivoting inside the block.
 struct InvJob {
     const double2* src;
     double2* dst;

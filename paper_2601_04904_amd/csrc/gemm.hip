@@ -44,21 +44,6 @@ __device__ inline double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// The product that owns tile bid: the last one whose first tile is not past
-// it.  The lanes of a wave look at 64 products at once, so the search is one
-// memory latency for up to 64 products (a scalar binary search is one per
-// level, about 2 us before the first operand load of a tile).
-__device__ inline int find_op(const GemmOp* __restrict__ ops, int nops, int bid, int lane) {
-    int last = 0;
-    for (int base = 0; base < nops; base += 64) {
-        const int i = min(base + lane, nops - 1);
-        const unsigned long long in = __ballot(base + lane < nops && ops[i].tile_begin <= bid);
-        if (in == 0) break;
-        last = base + 63 - __clzll(in);
-    }
-    return __builtin_amdgcn_readfirstlane(last);
-}
-
 // Global pointer in the global address space (the C operand's loads).
 #ifdef __HIP_DEVICE_COMPILE__
 typedef const __attribute__((address_space(1))) double2* gptr_t;
@@ -519,15 +504,18 @@ struct WaveTile<true, BM, BN> {
 // One workgroup computes a BM x BN complex tile of one product.
 template <bool MIXED, int BM, int BN>
 __global__ __launch_bounds__(kThreads)
-void zgemm_grouped(const GemmOp* __restrict__ ops, int nops) {
+void zgemm_grouped(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ order) {
     typedef typename std::conditional<MIXED, float2, double2>::type CT;     // element in LDS
     __shared__ CT As[2][kBK][BM + 1];
     __shared__ CT Bs[2][kBK][BN + 1];
 
-    const int bid = xcd_remap(blockIdx.x, gridDim.x);
-    const GemmOp* op = ops + find_op(ops, nops, bid, threadIdx.x & 63);
+    // which tile of which product: from the launch's order, or all tiles of the only
+    // product
+    const uint32_t at = order ? order[blockIdx.x] : (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    if (at == kNoTile) return;
+    const GemmOp* op = ops + (order ? at >> kTileBits : 0u);
+    const int local = (int)(order ? at & ((1u << kTileBits) - 1) : at);
     const int m = op->m, n = op->n, nterms = op->nterms;
-    const int local = bid - op->tile_begin;
     const int tm = local / op->tiles_n, tn = local - tm * op->tiles_n;
     const int i0 = tm * BM, j0 = tn * BN;
     const int tid = threadIdx.x;
@@ -668,8 +656,8 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, int nops) {
 }
 
 // Tile shapes of the grouped product (complex rows x complex columns).
-// Every op of a launch is tiled with the launch's shape: tiles_n and
-// tile_begin of the ops must be computed with gemm_tiles_shape().
+// Every op of a launch is tiled with the launch's shape: tiles_n of the ops and
+// the launch's tile order are those of that shape.
 struct TileShape { int bm, bn; };
 constexpr TileShape kShapes[kGemmShapes] = {{32, 32}, {64, 32}, {64, 64}};
 
@@ -681,19 +669,21 @@ int gemm_tiles_shape(int m, int n, int shape) {
 int gemm_tiles_n_shape(int n, int shape) { return (n + kShapes[shape].bn - 1) / kShapes[shape].bn; }
 
 template <bool MIXED>
-static void launch_mixed(const GemmOp* d_ops, int nops, int total_tiles, int shape, hipStream_t s) {
+static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid, int shape, hipStream_t s) {
     switch (shape) {
-        case 0: hipLaunchKernelGGL((zgemm_grouped<MIXED, 32, 32>), dim3(total_tiles), dim3(kThreads), 0, s, d_ops, nops); break;
-        case 1: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 32>), dim3(total_tiles), dim3(kThreads), 0, s, d_ops, nops); break;
-        default: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 64>), dim3(total_tiles), dim3(kThreads), 0, s, d_ops, nops); break;
+        case 0: hipLaunchKernelGGL((zgemm_grouped<MIXED, 32, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
+        case 1: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
+        default: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 64>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
     }
 }
 
-hipError_t launch_gemm_shape(const GemmOp* d_ops, int nops, int total_tiles, bool mixed, int shape, hipStream_t s) {
-    if (nops <= 0 || total_tiles <= 0) return hipSuccess;
+// d_order: the launch's tile order (grid entries, gemm_tile_order), or null for a
+// single product, whose tiles then are the grid.
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s) {
+    if (grid <= 0) return hipSuccess;
     if (shape < 0 || shape >= kGemmShapes) return hipErrorInvalidValue;
-    if (mixed) launch_mixed<true>(d_ops, nops, total_tiles, shape, s);
-    else launch_mixed<false>(d_ops, nops, total_tiles, shape, s);
+    if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
+    else launch_mixed<false>(d_ops, d_order, grid, shape, s);
     return hipGetLastError();
 }
 

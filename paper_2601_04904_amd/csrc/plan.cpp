@@ -43,7 +43,7 @@
 #include <vector>
 
 namespace btsq {
-hipError_t launch_gemm_shape(const GemmOp* d_ops, int nops, int total_tiles, bool mixed, int shape, hipStream_t s);
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s);
 int gemm_tiles_shape(int m, int n, int shape);
 int gemm_tiles_n_shape(int n, int shape);
 int gemm_shape_bm(int shape);
@@ -875,11 +875,12 @@ struct Launch {
     int type;         // 0 gemm, 4 add, 5 norms, 6 inverse panel step, 7 fused instances
     size_t off;       // element offset into the typed array
     int count;
-    int tiles;        // gemm: total tiles
+    int tiles;        // gemm: workgroups (length of its tile order)
     int mixed;        // gemm precision
     int maxd;         // inverse: max dim; panel step: kernel shape (inv_variant)
     int panel;
     size_t maxelems;  // add
+    size_t order_off = 0;   // gemm: its tile order
     double flops = 0; // algorithmic work of the launch
     double bytes = 0;
     int shape = 1;    // gemm: tile shape (gemm_shape_bm / gemm_shape_bn)
@@ -908,6 +909,7 @@ void gemm_work(const GemmOp* ops, int n, double& flops, double& bytes) {
 
 struct Program {
     std::vector<GemmOp> gemm;
+    std::vector<uint32_t> order;    // tile orders of the product launches
     std::vector<InvJob> inv;
     std::vector<AddOp> add;
     std::vector<NormJob> norm;
@@ -999,15 +1001,59 @@ int pick_shape(int mixed, int maxdim, const long* tiles) {
     return (v >= 0 && v < kGemmShapes) ? v : default_shape(mixed, tiles);
 }
 
+// Order in which the workgroups of a product launch take its tiles.  Workgroups go
+// round-robin over the 8 XCDs and each XCD works its own through in order, so each
+// gets a queue: products whose tiles take about as long (their k summed over the
+// terms, within a quarter) are cut into 8 contiguous runs of tiles, one per XCD, the
+// longest products first.  So the XCDs have equal work even where a launch mixes
+// one-term and three-term products, the short tiles come last and fill the tail,
+// and neighbouring tiles (which share operand rows or columns) still meet in one
+// L2.  One contiguous run of all tiles per XCD left the XCDs that got the long
+// products working alone.
+void gemm_tile_order(const GemmOp* ops, int n, int shape, std::vector<uint32_t>& out) {
+    std::vector<std::pair<double, int>> by(n);
+    for (int i = 0; i < n; ++i) {
+        double k = 0;
+        for (int t = 0; t < ops[i].nterms; ++t) k += ops[i].t[t].k;
+        by[i] = {k, i};
+    }
+    std::stable_sort(by.begin(), by.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+    std::vector<uint32_t> queue[kNumXcd], cls;
+    double load[kNumXcd] = {};
+    for (int i = 0; i < n;) {
+        const double k0 = by[i].first;
+        cls.clear();
+        for (; i < n && by[i].first >= 0.75 * k0; ++i) {
+            const int op = by[i].second, tiles = gemm_tiles_shape(ops[op].m, ops[op].n, shape);
+            for (int t = 0; t < tiles; ++t) cls.push_back((uint32_t)op << kTileBits | (uint32_t)t);
+        }
+        // the XCDs with the least work so far take one tile more where it does not divide
+        int xcd[kNumXcd], size[kNumXcd];
+        for (int x = 0; x < kNumXcd; ++x) xcd[x] = x;
+        std::stable_sort(xcd, xcd + kNumXcd, [&](int x, int y) { return load[x] < load[y]; });
+        for (int r = 0; r < kNumXcd; ++r)
+            size[xcd[r]] = (int)(cls.size() / kNumXcd) + (r < (int)(cls.size() % kNumXcd) ? 1 : 0);
+        size_t at = 0;
+        for (int x = 0; x < kNumXcd; ++x) {
+            queue[x].insert(queue[x].end(), cls.begin() + at, cls.begin() + at + size[x]);
+            at += size[x];
+            load[x] += std::max(k0, 1.0) * size[x];
+        }
+    }
+    size_t longest = 0;
+    for (auto& q : queue) longest = std::max(longest, q.size());
+    for (size_t i = 0; i < longest; ++i)
+        for (auto& q : queue) out.push_back(i < q.size() ? q[i] : kNoTile);
+}
+
 void set_shape(Program& pg, Launch& L, int shape) {
-    int tiles = 0;
     for (int i = 0; i < L.count; ++i) {
         GemmOp& g = pg.gemm[L.off + i];
-        g.tile_begin = tiles;
         g.tiles_n = gemm_tiles_n_shape(g.n, shape);
-        tiles += gemm_tiles_shape(g.m, g.n, shape);
     }
-    L.tiles = tiles;
+    L.order_off = pg.order.size();
+    gemm_tile_order(pg.gemm.data() + L.off, L.count, shape, pg.order);
+    L.tiles = (int)(pg.order.size() - L.order_off);
     L.shape = shape;
 }
 
@@ -1337,7 +1383,7 @@ struct bt_si_sq_plan {
         size_t dev_bytes = 0;
         bool dev_own = false;             // dev allocated on its own (did not fit the arena)
         std::vector<char> host;           // host copy the upload reads (kept as long as dev)
-        size_t off_gemm = 0, off_inv = 0, off_add = 0, off_norm = 0;
+        size_t off_gemm = 0, off_order = 0, off_inv = 0, off_add = 0, off_norm = 0;
         size_t off_frec = 0, off_fstep = 0, off_ftask = 0;
         std::vector<hipEvent_t> events;   // cross-stream events of the launch list
         hipGraphExec_t graph = nullptr;   // the launch list captured as a graph (BT_GRAPH)
@@ -1560,6 +1606,7 @@ hipError_t run_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c) {
 hipError_t enqueue_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c, hipStream_t main) {
     const Program& pg = c.prog;
     GemmOp* dg = reinterpret_cast<GemmOp*>(c.dev + c.off_gemm);
+    const uint32_t* dord = reinterpret_cast<const uint32_t*>(c.dev + c.off_order);
     InvJob* dj = reinterpret_cast<InvJob*>(c.dev + c.off_inv);
     AddOp* da = reinterpret_cast<AddOp*>(c.dev + c.off_add);
     NormJob* dn = reinterpret_cast<NormJob*>(c.dev + c.off_norm);
@@ -1589,7 +1636,7 @@ hipError_t enqueue_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c, hipStream
             if (ea) hipEventRecord(ea, s);
         }
         switch (L.type) {
-            case 0: e = launch_gemm_shape(dg + L.off, L.count, L.tiles, L.mixed != 0, L.shape, s); break;
+            case 0: e = launch_gemm_shape(dg + L.off, dord + L.order_off, L.tiles, L.mixed != 0, L.shape, s); break;
             case 4: e = launch_add(da + L.off, L.count, L.maxelems, s); break;
             case 5: e = launch_norms(dn + L.off, L.count, s); break;
             case 6: e = launch_inv_step(dj + L.off, L.count, L.maxd, L.panel, L.tiles, h->status, s); break;
@@ -1637,11 +1684,12 @@ std::vector<uint64_t> make_key(Mode mode, bool fp64_rerun, const std::vector<int
 // Device bytes of a compiled program's operation lists (each array starting
 // on a 256-byte boundary, as prepare_and_run lays them out).
 struct ProgLayout {
-    size_t off_inv, off_add, off_norm, off_frec, off_fstep, off_ftask, total;
+    size_t off_order, off_inv, off_add, off_norm, off_frec, off_fstep, off_ftask, total;
 };
 ProgLayout program_layout(const Program& pg) {
     ProgLayout L;
-    L.off_inv = align256(pg.gemm.size() * sizeof(GemmOp));
+    L.off_order = align256(pg.gemm.size() * sizeof(GemmOp));
+    L.off_inv = align256(L.off_order + pg.order.size() * sizeof(uint32_t));
     L.off_add = align256(L.off_inv + pg.inv.size() * sizeof(InvJob));
     L.off_norm = align256(L.off_add + pg.add.size() * sizeof(AddOp));
     L.off_frec = align256(L.off_norm + pg.norm.size() * sizeof(NormJob));
@@ -1749,6 +1797,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         char* stage = c->host.data();
         auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) memcpy(stage + off, src, bytes); };
         put(0, pg.gemm.data(), pg.gemm.size() * sizeof(GemmOp));
+        put(PL.off_order, pg.order.data(), pg.order.size() * sizeof(uint32_t));
         put(PL.off_inv, pg.inv.data(), pg.inv.size() * sizeof(InvJob));
         put(PL.off_add, pg.add.data(), pg.add.size() * sizeof(AddOp));
         put(PL.off_norm, pg.norm.data(), pg.norm.size() * sizeof(NormJob));
@@ -1769,6 +1818,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         c->norm_out = bt.norm_out;
         c->sel = sel;
         c->off_gemm = 0;
+        c->off_order = PL.off_order;
         c->off_inv = PL.off_inv;
         c->off_add = PL.off_add;
         c->off_norm = PL.off_norm;
@@ -2275,12 +2325,17 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     GemmOp* dops = nullptr;
     hipError_t e = hipMalloc(&buf, 2 * in_bytes + out_bytes);
     if (e != hipSuccess) { hipGetLastError(); return set_err(nullptr, BT_ERR_OOM, "autotune: scratch allocation failed"); }
-    e = hipMalloc(&dops, kMaxOps * sizeof(GemmOp));
+    // room for the operations and, behind them, the longest tile order: 2^13 tiles of
+    // 64 x 32 are at most 2^14 of 32 x 32, and the padding is below one per XCD
+    const size_t ops_bytes = align256(kMaxOps * sizeof(GemmOp));
+    const size_t order_bytes = ((size_t)1 << kTClasses) * 2 * sizeof(uint32_t) + 64 * kNumXcd;
+    e = hipMalloc(&dops, ops_bytes + order_bytes);
     if (e != hipSuccess) { hipGetLastError(); hipFree(buf); return set_err(nullptr, BT_ERR_OOM, "autotune: op list allocation failed"); }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&ev0);
     if (e == hipSuccess) e = hipEventCreate(&ev1);
     if (e == hipSuccess) e = hipMemsetAsync(buf, 0, 2 * in_bytes + out_bytes, s);
+    uint32_t* dorder = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(dops) + ops_bytes);
     const double2* A = reinterpret_cast<const double2*>(buf);
     const double2* B = reinterpret_cast<const double2*>(buf + in_bytes);
     double2* out = reinterpret_cast<double2*>(buf + 2 * in_bytes);
@@ -2288,6 +2343,7 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     for (auto& a : found) for (auto& b : a) for (auto& c : b) c = -1;
     std::string rep;
     std::vector<GemmOp> ops;
+    std::vector<uint32_t> order;
     for (int prec = 0; prec < 2 && e == hipSuccess; ++prec) {
         for (int mc = 1; mc < kMClasses && e == hipSuccess; ++mc) {
             const int m = 32 << mc;
@@ -2316,18 +2372,19 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
                 int best = -1;
                 float ms[kGemmShapes] = {0, 0, 0};
                 for (int sh = 0; sh < kGemmShapes && e == hipSuccess; ++sh) {
-                    int tiles = 0;
-                    for (auto& g : ops) {
-                        g.tile_begin = tiles;
-                        g.tiles_n = gemm_tiles_n_shape(m, sh);
-                        tiles += gemm_tiles_shape(m, m, sh);
-                    }
+                    for (auto& g : ops) g.tiles_n = gemm_tiles_n_shape(m, sh);
+                    order.clear();
+                    gemm_tile_order(ops.data(), (int)nops, sh, order);
+                    const int grid = (int)order.size();
                     e = hipMemcpyAsync(dops, ops.data(), ops.size() * sizeof(GemmOp), hipMemcpyHostToDevice, s);
-                    if (e == hipSuccess) e = launch_gemm_shape(dops, (int)nops, tiles, prec != 0, sh, s);   // warm-up
+                    if (e == hipSuccess)
+                        e = hipMemcpyAsync(dorder, order.data(), grid * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+                    if (e == hipSuccess) e = hipStreamSynchronize(s);     // the lists are reused below
+                    if (e == hipSuccess) e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, s);   // warm-up
                     if (e == hipSuccess) e = hipEventRecord(ev0, s);
                     constexpr int kReps = 3;
                     for (int r = 0; r < kReps && e == hipSuccess; ++r)
-                        e = launch_gemm_shape(dops, (int)nops, tiles, prec != 0, sh, s);
+                        e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, s);
                     if (e == hipSuccess) e = hipEventRecord(ev1, s);
                     if (e == hipSuccess) e = hipEventSynchronize(ev1);
                     if (e == hipSuccess) e = hipEventElapsedTime(&ms[sh], ev0, ev1);
@@ -2401,13 +2458,6 @@ bt_status bt_si_sq_diag_gemm(int32_t m, int32_t n, int32_t k,
     g.m = m;
     g.n = n;
     g.nterms = k > 0 ? 1 : 0;
-    if (shape < 0) {
-        long tiles[kGemmShapes];
-        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] = gemm_tiles_shape(m, n, sh);
-        shape = pick_shape(mixed, std::max(m, n), tiles);
-    }
-    g.tiles_n = gemm_tiles_n_shape(n, shape);
-    g.tile_begin = 0;
     g.mixed = mixed;
     g.beta = cplx(beta[0], beta[1]);
     g.t[0].A = reinterpret_cast<const double2*>(A);
@@ -2417,11 +2467,17 @@ bt_status bt_si_sq_diag_gemm(int32_t m, int32_t n, int32_t k,
     g.t[0].k = k;
     g.t[0].flags = (opA ? kTermAH : 0) | (opB ? kTermBH : 0);
     g.t[0].alpha = cplx(alpha[0], alpha[1]);
+    if (shape < 0) {
+        long tiles[kGemmShapes];
+        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] = gemm_tiles_shape(m, n, sh);
+        shape = pick_shape(mixed, std::max(m, n), tiles);
+    }
+    g.tiles_n = gemm_tiles_n_shape(n, shape);
     GemmOp* dop = nullptr;
     hipError_t e = hipMalloc(&dop, sizeof g);
     if (e != hipSuccess) return hip_err(nullptr, e, "hipMalloc");
     e = hipMemcpyAsync(dop, &g, sizeof g, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_gemm_shape(dop, 1, gemm_tiles_shape(m, n, shape), mixed != 0, shape, s);
+    if (e == hipSuccess) e = launch_gemm_shape(dop, nullptr, gemm_tiles_shape(m, n, shape), mixed != 0, shape, s);
     hipError_t e2 = hipStreamSynchronize(s);
     hipFree(dop);
     if (e != hipSuccess) return hip_err(nullptr, e, "diag_gemm launch");
@@ -2464,12 +2520,10 @@ bt_status bt_si_sq_diag_inverse(const void* src, void* dst, int32_t d, int32_t c
     DevStatus z{0, 0};
     e = hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(st, &z, sizeof z, hipMemcpyHostToDevice);
-    GemmOp* dg = reinterpret_cast<GemmOp*>(dev);
     InvJob* dj = reinterpret_cast<InvJob*>(dev + off_inv);
     for (const Launch& L : pg.launches) {
         if (e != hipSuccess) break;
         switch (L.type) {
-            case 0: e = launch_gemm_shape(dg + L.off, L.count, L.tiles, L.mixed != 0, L.shape, s); break;
             case 6: e = launch_inv_step(dj + L.off, L.count, L.maxd, L.panel, L.tiles, st, s); break;
             default: break;
         }

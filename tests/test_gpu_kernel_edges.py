@@ -125,3 +125,27 @@ def test_fused_tile_edges(torch, n, b, a, P, antih):
             assert rel_err(out[i][0].to_host(), R) < 1e-11
             assert rel_err(out[i][1].to_host(), L) < 1e-11
         bs.destroy()
+
+
+def test_products_of_different_length_in_a_launch(torch):
+    """Instances of very different block sizes and partition counts in one batch:
+    launches that mix one-term and six-term products of 3 to 130 rows, so that
+    tile orders have several classes and padding."""
+    import oracle
+    from tests._util import rel_err
+    from paper_2601_04904_amd import solver as S
+    from paper_2601_04904_amd.synth import gen_problem
+    specs = [(7, 130, 9, 3), (5, 65, 64, 1), (9, 3, 2, 4), (4, 33, 0, 2), (6, 64, 31, 2)]
+    probs = [gen_problem(n, b, a, 0.3, 0.05, 11 + b) for n, b, a, _ in specs]
+    dA = [S.DeviceBlocks.from_host(A) for A, _ in probs]
+    dB = [S.DeviceBlocks.from_host(B) for _, B in probs]
+    XR = [S.DeviceBlocks.empty(n, b, a) for n, b, a, _ in specs]
+    XL = [S.DeviceBlocks.empty(n, b, a) for n, b, a, _ in specs]
+    bs = S.BatchSolver([dict(n=n, b=b, a=a, partitions=P) for n, b, a, P in specs])
+    bs.solve(dA, dB, XR, XL)
+    bs.sync()
+    for i, (A, B) in enumerate(probs):
+        R, L = oracle.solve_dense(A, B)
+        assert rel_err(XR[i].to_host(), R) < 1e-11, i
+        assert rel_err(XL[i].to_host(), L) < 1e-11, i
+    bs.destroy()
