@@ -28,13 +28,10 @@
 // so that A' B'' is the interleaved complex product.  Operands rounded to FP32
 // while staging into LDS, v_mfma_f32_16x16x4f32 with FP32 accumulation, the
 // result added to the FP64 output in FP64.
-#include "common.h"
-#include <type_traits>
-#include <utility>
+#include "tile16.h"
 
 namespace btsq {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 16;          // complex k per LDS stage
@@ -655,11 +652,58 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ 
     wt.store(op, m, n, i0 + r0, j0 + c0, lane);
 }
 
+// Launches with at most about one larger tile per CU (kSmallShape): one 16 x 16 tile per
+// workgroup, its 4 waves each taking every fourth 16-deep chunk of k, the sums added
+// through LDS.  Four times the workgroups of 32 x 32 tiles and no barrier before the
+// end; what is left is the latency of the launch, of the descriptor and of the first
+// loads.  Against 32 x 32 tiles: 1 product of 32 4.0 -> 3.3 us, of 128 8.0 -> 4.5 us,
+// 3 of 256 14.0 -> 12.2 us; with many tiles per CU the operands are read too often
+// (6 of 512: 112 us in 64 x 32 tiles, 131 us here).
+constexpr int kSmallWaves = 4;
+__global__ __launch_bounds__(64 * kSmallWaves)
+void zgemm_small(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ order) {
+    union Work {
+        Turn turn[kSmallWaves][2];
+        double2 sum[kSmallWaves][4][64];
+    };
+    __shared__ Work L;
+    const uint32_t at = order ? order[blockIdx.x] : blockIdx.x;
+    if (at == kNoTile) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const OpRegs o(ops[order ? at >> kTileBits : 0u], lane);
+    const int tile = (int)(order ? at & ((1u << kTileBits) - 1) : at);
+    const int m = o.head(offsetof(GemmOp, m) / 4), n = o.head(offsetof(GemmOp, n) / 4);
+    const int tn = (n + 15) >> 4, ti = tile / tn;
+    const int i0 = ti * 16, j0 = (tile - ti * tn) * 16;
+    const int q = lane & 15, row = i0 + (lane >> 4) + 4 * wave;      // of the entry this lane writes
+    double2* C = op_c(o);
+    double2 cv = make_double2(0.0, 0.0);
+    if (C) {
+        const int ldc = o.head(offsetof(GemmOp, ldc) / 4);
+        cv = load16(fused_rsrc(C, m, n, ldc), (__mul24(row, ldc) + j0 + q) * 16);
+    }
+    v4d re, im;
+    tile16_sum<kSmallWaves>(o, m, n, i0, j0, wave, lane, L.turn[wave][0], L.turn[wave][1], re, im);
+    __syncthreads();                     // the sums take the place of the operands
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L.sum[wave][r][lane] = make_double2(re[r], im[r]);
+    __syncthreads();
+    double2 v = make_double2(0.0, 0.0);
+    if (C) cfma(v, op_beta(o), cv);
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        v.x += L.sum[w][wave][lane].x;
+        v.y += L.sum[w][wave][lane].y;
+    }
+    const int ldd = o.head(offsetof(GemmOp, ldd) / 4);
+    if (j0 + q < n) store16(fused_rsrc(op_d(o), m, n, ldd), (__mul24(row, ldd) + j0 + q) * 16, v);
+}
+
 // Tile shapes of the grouped product (complex rows x complex columns).
 // Every op of a launch is tiled with the launch's shape: tiles_n of the ops and
 // the launch's tile order are those of that shape.
 struct TileShape { int bm, bn; };
-constexpr TileShape kShapes[kGemmShapes] = {{32, 32}, {64, 32}, {64, 64}};
+constexpr TileShape kShapes[kGemmShapes + 1] = {{32, 32}, {64, 32}, {64, 64}, {16, 16}};    // last: kSmallShape
 
 int gemm_shape_bm(int shape) { return kShapes[shape].bm; }
 int gemm_shape_bn(int shape) { return kShapes[shape].bn; }
@@ -681,8 +725,10 @@ static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid,
 // single product, whose tiles then are the grid.
 hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
-    if (shape < 0 || shape >= kGemmShapes) return hipErrorInvalidValue;
-    if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
+    if (shape < 0 || shape > kSmallShape || (shape == kSmallShape && mixed)) return hipErrorInvalidValue;
+    if (shape == kSmallShape)
+        hipLaunchKernelGGL(zgemm_small, dim3(grid), dim3(64 * kSmallWaves), 0, s, d_ops, d_order);
+    else if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
     else launch_mixed<false>(d_ops, d_order, grid, shape, s);
     return hipGetLastError();
 }

@@ -979,26 +979,61 @@ int log2_class(long v, int lo, int hi) {
 // 61.5 r + 16 (64 x 64), so the small tile wins while it leaves fewer CUs with
 // a last tile to themselves (3 products of 512: 62, 76 and 73 us) and the
 // large one when there are many rounds (32 products: 649, 529 and 493 us).
+//
+// The 16 x 16 tiles of kSmallShape take 5.6 r + 4 on the same scale and are given
+// 6.5, since the fit is 10% low past five rounds.  They win while the launch has up
+// to about one 32 x 32 tile per CU, and where the outputs are so narrow that the
+// larger tiles are mostly padding: 1 product of 128: 8.0 (32 x 32) and 4.5 us, 3 of
+// 256: 14.0 and 12.2, 4 of 256: 14.3 and 14.2, 2 of 384: 30.1 (64 x 32) and 27.1;
+// but 3 of 384: 32.1 and 36.2, 2 of 512: 42.6 and 48.1.
 int default_shape(int mixed, const long* tiles) {
     if (mixed) return tiles[1] < 512 ? 0 : 1;
-    constexpr double kPerTile[kGemmShapes] = {20.5, 33.0, 61.5}, kFixed[kGemmShapes] = {4.0, 10.0, 16.0};
+    constexpr double kPerTile[kGemmShapes + 1] = {20.5, 33.0, 61.5, 6.5}, kFixed[kGemmShapes + 1] = {4.0, 10.0, 16.0, 4.0};
     constexpr long kCUs = 256;
     int best = 0;
     double tb = 0.0;
-    for (int sh = 0; sh < kGemmShapes; ++sh) {
+    for (int sh = 0; sh <= kSmallShape; ++sh) {
+        if (sh == kSmallShape && tiles[sh] < 0) break;
         const double t = kPerTile[sh] * (double)((tiles[sh] + kCUs - 1) / kCUs) + kFixed[sh];
         if (sh == 0 || t < tb) { best = sh; tb = t; }
     }
     return best;
 }
 
-// tiles: the launch's tile count in each shape
+// Whether kSmallShape may compute the product: its 32-bit byte offsets, 24-bit
+// index products and the tile number in an order entry.
+bool small_fits(const GemmOp& g) {
+    constexpr int kLd = 1 << 16;
+    auto ok = [](int ld) { return ld >= 1 && ld <= kLd; };
+    if (g.mixed || g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc)) ||
+        gemm_tiles_shape(g.m, g.n, kSmallShape) > (1 << kTileBits))
+        return false;
+    for (int t = 0; t < g.nterms; ++t)
+        if (g.t[t].k > kInvMaxDim || !ok(g.t[t].lda) || !ok(g.t[t].ldb)) return false;
+    return true;
+}
+
+// The launch's tiles in each shape; kSmallShape: -1 if it may not compute all of them.
+void count_tiles(const GemmOp* ops, int n, long* tiles) {
+    for (int sh = 0; sh <= kSmallShape; ++sh) tiles[sh] = 0;
+    bool fits = true;
+    for (int i = 0; i < n; ++i) {
+        for (int sh = 0; sh <= kSmallShape; ++sh) tiles[sh] += gemm_tiles_shape(ops[i].m, ops[i].n, sh);
+        fits = fits && small_fits(ops[i]);
+    }
+    if (!fits) tiles[kSmallShape] = -1;
+}
+
+// The table holds the fastest of the three larger shapes; where the rule takes
+// kSmallShape, it is faster than each of them.
 int pick_shape(int mixed, int maxdim, const long* tiles) {
+    const int rule = default_shape(mixed, tiles);
+    if (rule == kSmallShape) return rule;
     tune_init();
     const int mc = log2_class(maxdim, 5, 5 + kMClasses - 1);
     const int tc = log2_class(std::max(1L, tiles[1]), 0, kTClasses - 1);
     const int v = g_tune[mixed ? 1 : 0][mc][tc].load();
-    return (v >= 0 && v < kGemmShapes) ? v : default_shape(mixed, tiles);
+    return (v >= 0 && v < kGemmShapes) ? v : rule;
 }
 
 // Order in which the workgroups of a product launch take its tiles.  Workgroups go
@@ -1058,11 +1093,11 @@ void set_shape(Program& pg, Launch& L, int shape) {
 }
 
 void assign_shape(Program& pg, Launch& L) {
-    long tiles[kGemmShapes] = {};
+    long tiles[kGemmShapes + 1];
     int maxdim = 1;
+    count_tiles(pg.gemm.data() + L.off, L.count, tiles);
     for (int i = 0; i < L.count; ++i) {
         const GemmOp& g = pg.gemm[L.off + i];
-        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] += gemm_tiles_shape(g.m, g.n, sh);
         maxdim = std::max(maxdim, std::max(g.m, g.n));
     }
     set_shape(pg, L, pick_shape(L.mixed, maxdim, tiles));
@@ -2468,8 +2503,8 @@ bt_status bt_si_sq_diag_gemm(int32_t m, int32_t n, int32_t k,
     g.t[0].flags = (opA ? kTermAH : 0) | (opB ? kTermBH : 0);
     g.t[0].alpha = cplx(alpha[0], alpha[1]);
     if (shape < 0) {
-        long tiles[kGemmShapes];
-        for (int sh = 0; sh < kGemmShapes; ++sh) tiles[sh] = gemm_tiles_shape(m, n, sh);
+        long tiles[kGemmShapes + 1];
+        count_tiles(&g, 1, tiles);
         shape = pick_shape(mixed, std::max(m, n), tiles);
     }
     g.tiles_n = gemm_tiles_n_shape(n, shape);

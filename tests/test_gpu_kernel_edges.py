@@ -46,6 +46,29 @@ def test_product_stage_edges(torch, m, n, k, alpha):
                 assert (np.abs(out - ref) <= bound).all(), (opA, opB, shape)
 
 
+@pytest.mark.parametrize("k", [0, 1, 15, 16, 17, 63, 64, 65, 80, 129, 1024])
+@pytest.mark.parametrize("m,n", [(1, 1), (16, 17), (15, 33), (1, 200), (144, 16), (129, 127)])
+def test_small_launch_tiles(torch, m, n, k):
+    """The shape that the default rule takes for one small product: 16 x 16 tiles
+    whose k is split over the waves of a workgroup."""
+    from paper_2601_04904_amd.solver import diag_gemm
+    rng = np.random.default_rng(m * 1000 + n * 50 + k)
+    beta = 0.25 - 1.5j
+    for opA in (0, 1):
+        for opB in (0, 1):
+            for alpha in (1.0, -1.0, 0.5 - 2.0j):
+                A = crand(rng, *((k, m) if opA else (m, k)))
+                B = crand(rng, *((n, k) if opB else (k, n)))
+                C = crand(rng, m, n)
+                a, b = (A.conj().T if opA else A), (B.conj().T if opB else B)
+                dA, dB, dC = (torch.from_numpy(x).cuda() for x in (A, B, C))
+                for Cin in (None, dC):
+                    c0 = 0.0 if Cin is None else beta * C
+                    bound = (k + 4) * EPS * 4 * (np.abs(c0) + abs(alpha) * (np.abs(a) @ np.abs(b)))
+                    out = diag_gemm(alpha, dA, opA, dB, opB, beta=beta, Cin=Cin).cpu().numpy()
+                    assert (np.abs(out - (c0 + alpha * (a @ b))) <= bound).all(), (opA, opB, alpha, Cin is None)
+
+
 def test_more_products_than_one_search(torch):
     """130 instances: launches of more than 128 products and inverses."""
     import oracle
