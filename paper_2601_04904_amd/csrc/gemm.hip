@@ -32,7 +32,6 @@
 
 namespace btsq {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 16;          // complex k per LDS stage
 constexpr int kThreads = 256;    // 4 waves, 2 x 2 over the tile
@@ -657,9 +656,11 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ 
 // through LDS.  Four times the workgroups of 32 x 32 tiles and no barrier before the
 // end; what is left is the latency of the launch, of the descriptor and of the first
 // loads.  Against 32 x 32 tiles: 1 product of 32 4.0 -> 3.3 us, of 128 8.0 -> 4.5 us,
-// 3 of 256 14.0 -> 12.2 us; with many tiles per CU the operands are read too often
+// 3 of 256 14.0 -> 12.2 us (mixed, where the sums of the waves are added in FP64: 5.1 ->
+// 3.2, 9.3 -> 4.2, 15.5 -> 9.6 us); with many tiles per CU the operands are read too often
 // (6 of 512: 112 us in 64 x 32 tiles, 131 us here).
 constexpr int kSmallWaves = 4;
+template <bool MIXED>
 __global__ __launch_bounds__(64 * kSmallWaves)
 void zgemm_small(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ order) {
     union Work {
@@ -675,15 +676,15 @@ void zgemm_small(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ or
     const int m = o.head(offsetof(GemmOp, m) / 4), n = o.head(offsetof(GemmOp, n) / 4);
     const int tn = (n + 15) >> 4, ti = tile / tn;
     const int i0 = ti * 16, j0 = (tile - ti * tn) * 16;
-    const int q = lane & 15, row = i0 + (lane >> 4) + 4 * wave;      // of the entry this lane writes
+    const int q = lane & 15, row = i0 + tile16_row<MIXED>(lane, wave);     // of the entry this lane writes
     double2* C = op_c(o);
     double2 cv = make_double2(0.0, 0.0);
     if (C) {
         const int ldc = o.head(offsetof(GemmOp, ldc) / 4);
         cv = load16(fused_rsrc(C, m, n, ldc), (__mul24(row, ldc) + j0 + q) * 16);
     }
-    v4d re, im;
-    tile16_sum<kSmallWaves>(o, m, n, i0, j0, wave, lane, L.turn[wave][0], L.turn[wave][1], re, im);
+    typename Tile16Acc<MIXED>::type re, im;
+    tile16_sum<kSmallWaves, MIXED>(o, m, n, i0, j0, wave, lane, L.turn[wave][0], L.turn[wave][1], re, im);
     __syncthreads();                     // the sums take the place of the operands
 #pragma unroll
     for (int r = 0; r < 4; ++r) L.sum[wave][r][lane] = make_double2(re[r], im[r]);
@@ -717,6 +718,7 @@ static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid,
     switch (shape) {
         case 0: hipLaunchKernelGGL((zgemm_grouped<MIXED, 32, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
         case 1: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
+        case kSmallShape: hipLaunchKernelGGL(zgemm_small<MIXED>, dim3(grid), dim3(64 * kSmallWaves), 0, s, d_ops, d_order); break;
         default: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 64>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
     }
 }
@@ -725,10 +727,8 @@ static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid,
 // single product, whose tiles then are the grid.
 hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
-    if (shape < 0 || shape > kSmallShape || (shape == kSmallShape && mixed)) return hipErrorInvalidValue;
-    if (shape == kSmallShape)
-        hipLaunchKernelGGL(zgemm_small, dim3(grid), dim3(64 * kSmallWaves), 0, s, d_ops, d_order);
-    else if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
+    if (shape < 0 || shape > kSmallShape) return hipErrorInvalidValue;
+    if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
     else launch_mixed<false>(d_ops, d_order, grid, shape, s);
     return hipGetLastError();
 }

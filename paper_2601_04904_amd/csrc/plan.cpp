@@ -971,8 +971,9 @@ int log2_class(long v, int lo, int hi) {
     return std::min(std::max(c, lo), hi) - lo;
 }
 
-// Default rule.  Mixed: 32 x 32 tiles below 512 tiles of 64 x 32, 64 x 32
-// tiles above.  FP64: the shape of smallest estimated time.  A launch is
+// Default rule.  Mixed: 16 x 16 tiles for small launches (below), then 32 x 32 tiles
+// below 512 tiles of 64 x 32, 64 x 32 tiles above.  FP64: the shape of smallest
+// estimated time.  A launch is
 // bound by the CU with the most tiles, r = ceil(tiles / 256) of them; measured
 // on launches of 1 to 64 square products with r from 1 to 64, the time in us
 // at k = 512 is within 8% of 20.5 r + 4 (32 x 32), 33 r + 10 (64 x 32) and
@@ -986,15 +987,22 @@ int log2_class(long v, int lo, int hi) {
 // larger tiles are mostly padding: 1 product of 128: 8.0 (32 x 32) and 4.5 us, 3 of
 // 256: 14.0 and 12.2, 4 of 256: 14.3 and 14.2, 2 of 384: 30.1 (64 x 32) and 27.1;
 // but 3 of 384: 32.1 and 36.2, 2 of 512: 42.6 and 48.1.
+//
+// Mixed, on the same scale: 16 x 16 tiles take 4 r + 4 and 32 x 32 tiles 11 r + 16
+// (1 product of 128: 4.2 and 9.3 us, 4 of 256: 11.6 and 15.8, 2 of 512: 34.9 and
+// 38.2, 3 of 512: 49.8 and 49.2).
 int default_shape(int mixed, const long* tiles) {
-    if (mixed) return tiles[1] < 512 ? 0 : 1;
+    auto rounds = [](long t) { return (t + 255) / 256; };
+    if (mixed) {
+        if (tiles[kSmallShape] >= 0 && 4 * rounds(tiles[kSmallShape]) + 4 < 11 * rounds(tiles[0]) + 16) return kSmallShape;
+        return tiles[1] < 512 ? 0 : 1;
+    }
     constexpr double kPerTile[kGemmShapes + 1] = {20.5, 33.0, 61.5, 6.5}, kFixed[kGemmShapes + 1] = {4.0, 10.0, 16.0, 4.0};
-    constexpr long kCUs = 256;
     int best = 0;
     double tb = 0.0;
     for (int sh = 0; sh <= kSmallShape; ++sh) {
         if (sh == kSmallShape && tiles[sh] < 0) break;
-        const double t = kPerTile[sh] * (double)((tiles[sh] + kCUs - 1) / kCUs) + kFixed[sh];
+        const double t = kPerTile[sh] * (double)rounds(tiles[sh]) + kFixed[sh];
         if (sh == 0 || t < tb) { best = sh; tb = t; }
     }
     return best;
@@ -1005,7 +1013,7 @@ int default_shape(int mixed, const long* tiles) {
 bool small_fits(const GemmOp& g) {
     constexpr int kLd = 1 << 16;
     auto ok = [](int ld) { return ld >= 1 && ld <= kLd; };
-    if (g.mixed || g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc)) ||
+    if (g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc)) ||
         gemm_tiles_shape(g.m, g.n, kSmallShape) > (1 << kTileBits))
         return false;
     for (int t = 0; t < g.nterms; ++t)

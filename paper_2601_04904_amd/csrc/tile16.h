@@ -1,6 +1,7 @@
 // A 16 x 16 tile of a grouped product by one wave, shared by the fused
 // small-instance kernel and the small-launch product kernel: operands go from
-// memory to the layout of v_mfma_f64_16x16x4 without workgroup barriers.
+// memory to the layout of v_mfma_f64_16x16x4 (v_mfma_f32_16x16x4f32, which has the
+// same operand layout, for products in complex64) without workgroup barriers.
 #pragma once
 #include "gauss.h"
 #include <cstddef>
@@ -53,18 +54,28 @@ __device__ inline void store16(__amdgpu_buffer_rsrc_t r, int off, double2 v) {
 // 16 lanes and turned through a piece of LDS of the wave's own (no barrier).
 typedef double2 Turn[16][17];
 
-// sum_t alpha_t op(A_t) op(B_t) over the 16 x 16 tile at (i0, j0), by one wave:
-// entry (i0 + lane/16 + 4r, j0 + lane%16) in register r.  The k range of every term
+// Accumulators of a tile: register r is row tile16_row of column lane%16.
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <bool MIXED> struct Tile16Acc { typedef v4d type; };
+template <> struct Tile16Acc<true> { typedef v4f type; };
+template <bool MIXED>
+__device__ inline int tile16_row(int lane, int r) {
+    return MIXED ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
+}
+
+// sum_t alpha_t op(A_t) op(B_t) over the 16 x 16 tile at (i0, j0), by one wave;
+// MIXED: operands (after conjugation and alpha) rounded to FP32 and accumulated in
+// FP32.  The k range of every term
 // is taken 16 at a time, chunks w, w + KW, ... of each (KW waves share a tile); the
 // next chunk's loads (of the same or the next term) are issued before the current
 // chunk's MFMAs.  Entries of A and B past k are cleared; rows and columns outside the
 // product only reach entries that are not stored.
-template <int KW>
+template <int KW, bool MIXED>
 __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0, int w, int lane, Turn& XA, Turn& XB,
-                                  v4d& re, v4d& im) {
+                                  typename Tile16Acc<MIXED>::type& re, typename Tile16Acc<MIXED>::type& im) {
     const int nt = o.head(offsetof(GemmOp, nterms) / 4);
     const int q = lane & 15, kq = lane >> 4;
-    re = im = v4d{0.0, 0.0, 0.0, 0.0};
+    re = im = typename Tile16Acc<MIXED>::type{};
     // The chunk to load next: term s at offset c0.  Element t of a lane lies along
     // k (row kq + 4 t of the tile, k = q) or across (row or column q, k = 4 t + kq):
     // byte offsets va + t da (vb + t db), from one chunk to the wave's next ka (kb) more.
@@ -161,10 +172,18 @@ __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0,
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (4 * t >= c.left) break;                 // wave-uniform
-            re = mfma64(c.a[t].x, c.b[t].x, re);
-            im = mfma64(c.a[t].x, c.b[t].y, im);
-            re = mfma64_nega(c.a[t].y, c.b[t].y, re);
-            im = mfma64(c.a[t].y, c.b[t].x, im);
+            if constexpr (MIXED) {
+                const float ax = (float)c.a[t].x, ay = (float)c.a[t].y, bx = (float)c.b[t].x, by = (float)c.b[t].y;
+                re = __builtin_amdgcn_mfma_f32_16x16x4f32(ax, bx, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f32_16x16x4f32(ax, by, im, 0, 0, 0);
+                re = __builtin_amdgcn_mfma_f32_16x16x4f32(-ay, by, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, bx, im, 0, 0, 0);
+            } else {
+                re = mfma64(c.a[t].x, c.b[t].x, re);
+                im = mfma64(c.a[t].x, c.b[t].y, im);
+                re = mfma64_nega(c.a[t].y, c.b[t].y, re);
+                im = mfma64(c.a[t].y, c.b[t].x, im);
+            }
         }
     };
     advance();

@@ -54,6 +54,7 @@ def test_small_launch_tiles(torch, m, n, k):
     from paper_2601_04904_amd.solver import diag_gemm
     rng = np.random.default_rng(m * 1000 + n * 50 + k)
     beta = 0.25 - 1.5j
+    EPS32 = np.finfo(np.float32).eps
     for opA in (0, 1):
         for opB in (0, 1):
             for alpha in (1.0, -1.0, 0.5 - 2.0j):
@@ -66,6 +67,10 @@ def test_small_launch_tiles(torch, m, n, k):
                     c0 = 0.0 if Cin is None else beta * C
                     bound = (k + 4) * EPS * 4 * (np.abs(c0) + abs(alpha) * (np.abs(a) @ np.abs(b)))
                     out = diag_gemm(alpha, dA, opA, dB, opB, beta=beta, Cin=Cin).cpu().numpy()
+                    assert (np.abs(out - (c0 + alpha * (a @ b))) <= bound).all(), (opA, opB, alpha, Cin is None)
+                    # products in complex64, beta C in FP64
+                    out = diag_gemm(alpha, dA, opA, dB, opB, beta=beta, Cin=Cin, mixed=True).cpu().numpy()
+                    bound += (k + 4) * EPS32 * 4 * abs(alpha) * (np.abs(a) @ np.abs(b))
                     assert (np.abs(out - (c0 + alpha * (a @ b))) <= bound).all(), (opA, opB, alpha, Cin is None)
 
 
