@@ -120,8 +120,7 @@ typedef enum {
                                where those levels are short (small b).  Needs every
                                diagonal block and the tip of size <= 64 and BT_FP64
                                without BT_PLAIN (else BT_ERR_INVALID).  Results agree with
-                               the grouped path to rounding (other summation order, and
-                               the inverse pivots on the rows of the block). */
+                               the grouped path to rounding (other summation order). */
 
 typedef struct {
     int32_t n;                  /* number of diagonal blocks, >= 1 */
@@ -292,8 +291,9 @@ int32_t bt_si_sq_last_launch_count(bt_si_sq_handle h);
 typedef enum {
     BT_KERNEL_PRODUCT_FP64 = 0,   /* grouped complex products, FP64 MFMA */
     BT_KERNEL_PRODUCT_MIXED = 1,  /* grouped complex products, FP32 MFMA */
-    BT_KERNEL_INV_PANEL = 2,      /* inverse: panel elimination (the launches also read the
-                                     block to invert and write the result) */
+    BT_KERNEL_INV_PANEL = 2,      /* inverse: panel elimination, or the whole inverse of
+                                     a small block (the launches also read the block to
+                                     invert and write the result) */
     BT_KERNEL_INV_INIT = 3,       /* unused (kept for numbering) */
     BT_KERNEL_INV_FINISH = 4,     /* unused (kept for numbering) */
     BT_KERNEL_SUM = 5,            /* elementwise block sums */
@@ -327,7 +327,9 @@ bt_status bt_si_sq_profile_stats(bt_si_sq_handle h, bt_kernel_stat* out, int32_t
  * precision (0 FP64, 1 mixed), size class (log2 of its largest output
  * dimension, 32..1024 -> 0..5) and work class (log2 of its 64 x 32 tile
  * count, 1..8192 -> 0..13); the shape of a class comes from a process-wide
- * tuning table, or from a default rule for classes never tuned.  Handles
+ * tuning table, or from a default rule for classes never tuned.  Small
+ * launches take 16 x 16 tiles whatever the table says (faster than each of
+ * the three there; the shape is not one of the table's).  Handles
  * compile their launch lists when a pointer set is first used, so a table
  * change reaches launch lists compiled after it. */
 #define BT_TILE_SHAPES 3

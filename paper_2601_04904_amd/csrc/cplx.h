@@ -22,7 +22,7 @@ __device__ inline double2 sel2(bool c, double2 a, double2 b) {
     return make_double2(c ? a.x : b.x, c ? a.y : b.y);
 }
 
-// acc += a b and acc -= a b, four fused multiply-adds each
+// acc += a b, four fused multiply-adds
 __device__ inline void cfma(double2& acc, double2 a, double2 b) {
     acc.x = fma(a.x, b.x, acc.x);
     acc.x = fma(-a.y, b.y, acc.x);
@@ -30,17 +30,11 @@ __device__ inline void cfma(double2& acc, double2 a, double2 b) {
     acc.y = fma(a.y, b.x, acc.y);
 }
 
-__device__ inline void cfms(double2& acc, double2 a, double2 b) {
-    acc.x = fma(-a.x, b.x, acc.x);
-    acc.x = fma(a.y, b.y, acc.x);
-    acc.y = fma(-a.x, b.y, acc.y);
-    acc.y = fma(-a.y, b.x, acc.y);
-}
-
 // 1 / v = conj(v) / |v|^2.  v is first scaled by a power of two so that
-// |re| + |im| lies in [0.5, 1), which puts |v|^2 in [0.125, 1); the reciprocal of |v|^2 is the hardware estimate refined by two Newton steps
-// r <- r (2 - s r) (each at least doubles the number of correct bits).  A
-// zero, infinite or NaN v gives a NaN result, which the caller flags.
+// |re| + |im| lies in [0.5, 1), which puts |v|^2 in [0.125, 1); the reciprocal of
+// |v|^2 is the hardware estimate refined by two Newton steps r <- r (2 - s r) (each
+// at least doubles the number of correct bits).  A zero, infinite or NaN v gives a
+// NaN result, which the caller flags.
 __device__ inline double2 crecip(double2 v) {
     int e;
     const double m = fabs(v.x) + fabs(v.y);
@@ -73,24 +67,15 @@ __device__ inline unsigned wave_umax(unsigned x) {
     return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-// Pivot key (32 bits): bits 62..41 of the double |re| + |im| (its exponent
-// and the top 11 bits of its mantissa; non-finite values clamped to the
-// largest finite double) above 1023 - row in the low 10 bits.  Non-negative
-// doubles order like their bit patterns, so the largest key is the largest
-// magnitude to 11 mantissa bits (any candidate within a relative 2^-11 of the
-// largest is as good a pivot) and, among those, the lowest row.  Rows are
-// below 1024.  0 means "no candidate" (it is also the key of a zero entry in
-// row 1023; either way the column has no usable pivot).
-__device__ inline unsigned pivot_key(double2 v, int row) {
-    double m = fabs(v.x) + fabs(v.y);
-    if (!(m <= DBL_MAX)) m = DBL_MAX;
-    const unsigned long long bits = (unsigned long long)__double_as_longlong(m);
-    return ((unsigned)(bits >> 41) << 10) | (unsigned)(1023 - row);
-}
-
-// The same key from a row's mask and row bits (both 0 for a row that is not a
-// candidate).  A non-finite value keeps the largest exponent, so it is chosen and
-// its reciprocal is NaN, which the caller flags.
+// Pivot key (32 bits): bits 62..41 of the double |re| + |im| (its exponent and the
+// top 11 bits of its mantissa) above 1023 - row in the low 10 bits, from the row's
+// mask and row bits (both 0 for a row that is not a candidate).  Non-negative
+// doubles order like their bit patterns, so the largest key is the largest magnitude
+// to 11 mantissa bits (any candidate within a relative 2^-11 of the largest is as
+// good a pivot) and, among those, the lowest row.  Rows are below 1024.  0 means "no
+// candidate" (it is also the key of a zero entry in row 1023; either way the column
+// has no usable pivot).  A non-finite value keeps the largest exponent, so it is
+// chosen and its reciprocal is NaN, which the caller flags.
 constexpr unsigned kKeyBits = ~1023u;
 __device__ inline unsigned key_row_bits(int row) { return (unsigned)(1023 - row); }
 __device__ inline unsigned pivot_key(double2 v, unsigned mask, unsigned row_bits) {

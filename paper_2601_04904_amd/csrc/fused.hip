@@ -29,7 +29,6 @@
 
 namespace btsq {
 
-
 // Values every lane holds alike, moved to scalar registers so that branches and
 // addresses on them stay uniform.
 __device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }

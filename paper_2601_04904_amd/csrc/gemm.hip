@@ -2,8 +2,9 @@
 //
 // Every block update of the forward and backward sweeps is a dense complex
 // product (or a short sum of them) on b x b, b x a and a x a blocks.  One
-// launch executes a list of independent products, each tiled into 64 x 32
-// complex output tiles; a workgroup owns one tile of one product.
+// launch executes a list of independent products, each cut into complex output
+// tiles of the launch's shape (64 x 64, 64 x 32, 32 x 32, or 16 x 16 for small
+// launches); a workgroup owns one tile of one product.
 //
 // FP64 path: v_mfma_f64_16x16x4 on the real and imaginary parts, four MFMAs per
 // 16 x 16 x 4 complex block (an element is one 16-byte (re, im) pair in memory,
@@ -19,7 +20,7 @@
 // around every stage, which halves the rate of the 16x16x4 instruction (36
 // against 77.5 TFLOP/s in a loop of it alone).
 //
-// Mixed path: complex arithmetic on real MFMA by a 2 x 2 real embedding.  A
+// Mixed path (all but the 16 x 16 tiles): complex arithmetic on real MFMA by a 2 x 2 real embedding.  A
 // complex m x k matrix A stored as interleaved (re, im) is read as the real
 // m x 2k matrix A', and op(B) (k x n complex) is expanded on the fly into the
 // real 2k x 2n matrix
@@ -31,7 +32,6 @@
 #include "tile16.h"
 
 namespace btsq {
-
 
 constexpr int kBK = 16;          // complex k per LDS stage
 constexpr int kThreads = 256;    // 4 waves, 2 x 2 over the tile

@@ -25,7 +25,8 @@
 // other, the two halves of the reduced system, SQ backward beside SI
 // backward - therefore share launches.  The A-chain runs on a second stream;
 // launch lists are compiled once per pointer set (optionally captured as a
-// HIP graph), and product tile shapes come from the tuning table.
+// HIP graph), and product tile shapes come from the tuning table or, for small
+// launches and classes never tuned, from a rule.
 #include "../../include/bt_si_sq.h"
 #include "common.h"
 
@@ -954,7 +955,8 @@ GemmOp make_gemm_op(const OpRec& o) {
 // size class of its largest output (log2 of max(m, n), 5..10) and the class of
 // its work (log2 of its 64 x 32 tile count, 0..13); the shape comes from the
 // tuning table (filled by bt_si_sq_autotune or loaded with
-// bt_si_sq_tune_table) or, for classes never tuned, from the default rule.
+// bt_si_sq_tune_table) or, for small launches and classes never tuned, from the
+// default rule.
 constexpr int kMClasses = 6, kTClasses = 14;
 std::atomic<int> g_tune[2][kMClasses][kTClasses];
 std::once_flag g_tune_once;
