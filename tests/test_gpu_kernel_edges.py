@@ -95,6 +95,28 @@ def test_more_products_than_one_search(torch):
     bs.destroy()
 
 
+@pytest.mark.parametrize("sizes", [(113, 300), (256, 513), (40, 100, 128, 257), (200, 112)])
+def test_inverse_shapes_in_one_level(torch, sizes):
+    """Instances whose inverses have different kernel shapes, levelled together."""
+    import oracle
+    from tests._util import rel_err
+    from paper_2601_04904_amd import solver as S
+    from paper_2601_04904_amd.synth import gen_problem
+    probs = [gen_problem(2, b, 0, 0.3, 0.05, b) for b in sizes]
+    dA = [S.DeviceBlocks.from_host(A) for A, _ in probs]
+    dB = [S.DeviceBlocks.from_host(B) for _, B in probs]
+    XR = [S.DeviceBlocks.empty(A.n, A.b, A.a) for A, _ in probs]
+    XL = [S.DeviceBlocks.empty(A.n, A.b, A.a) for A, _ in probs]
+    bs = S.BatchSolver([dict(n=A.n, b=A.b, a=A.a) for A, _ in probs])
+    bs.solve(dA, dB, XR, XL)
+    bs.sync()
+    for i, (A, B) in enumerate(probs):
+        R, L = oracle.solve_dense(A, B)
+        assert rel_err(XR[i].to_host(), R) < 1e-11, i
+        assert rel_err(XL[i].to_host(), L) < 1e-11, i
+    bs.destroy()
+
+
 @pytest.mark.parametrize("d", [3, 4, 5, 31, 48, 49, 63, 64, 65, 79, 111, 112, 113, 127, 128, 129, 145, 255, 256, 257,
                                511, 512, 513, 1023])
 def test_inverse_shape_edges(torch, d):
