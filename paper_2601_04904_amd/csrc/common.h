@@ -18,7 +18,7 @@ struct GemmTerm {
 
 constexpr int kMaxTerms = 6;
 constexpr int kGemmShapes = 3;     // product tile shapes: 32x32, 64x32, 64x64 complex
-constexpr int kSmallShape = 3;     // 16x16, chosen for small FP64 launches only
+constexpr int kSmallShape = 3;     // 16x16, chosen by rule for small launches only
 constexpr int kTermAH = 1;
 constexpr int kTermBH = 2;
 
