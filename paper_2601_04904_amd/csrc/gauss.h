@@ -19,6 +19,15 @@ __device__ inline v4d mfma64_nega(double a, double b, v4d c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
 }
 
+// Between LDS writes and reads of the same places by different lanes of one wave: the
+// wave's LDS instructions complete in order, so nothing waits, but per lane the
+// addresses differ and the compiler would be free to change the order.
+__device__ inline void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Value of a double in lane src (wave-uniform), in every lane.
 __device__ inline double lane_value(double x, int src) {
     const long long b = __double_as_longlong(x);
@@ -336,7 +345,8 @@ __device__ void small_inverse(const double2* src, double2* dst, int d, int tag, 
             if (nc <= 0) return;
             const int next = j0 + kGrp;                // the next group's owner goes first where waves share a SIMD
             if (wave != next / kInvNB) __builtin_amdgcn_s_setprio(0);
-            take_group_rows(W, 0, m, i, piv, L.G[wave]);
+            take_group_rows(W, 0, m, i, piv, L.G[wave]);      // (last group's reads: a barrier ago)
+            wave_lds_fence();
             double2 g = L.G[wave][i][m];
             // columns the group has, and its own place in its owner's block
             if (i >= count || (wave == cw && (m >> 2) == grp)) g = make_double2(0.0, 0.0);

@@ -54,6 +54,15 @@ __device__ inline void store16(__amdgpu_buffer_rsrc_t r, int off, double2 v) {
 // 16 lanes and turned through a piece of LDS of the wave's own (no barrier).
 typedef double2 Turn[16][17];
 
+__device__ inline void turn16(double2* v, Turn& X, int q, int kq) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) X[q][kq + 4 * t] = v[t];
+    wave_lds_fence();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = X[4 * t + kq][q];
+    wave_lds_fence();                    // before the next chunk's writes
+}
+
 // Accumulators of a tile: register r is row tile16_row of column lane%16.
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <bool MIXED> struct Tile16Acc { typedef v4d type; };
@@ -133,20 +142,14 @@ __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0,
             c.b[t] = load16(rb, vb + t * db);
         }
     };
-    auto turn = [&](double2* v, Turn& X) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) X[q][kq + 4 * t] = v[t];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = X[4 * t + kq][q];
-    };
     auto flip = [](double v) {
         return __longlong_as_double(__double_as_longlong(v) ^ (long long)0x8000000000000000ull);
     };
     auto multiply = [&](Chunk& c) {
         const bool one = c.alpha.y == 0.0 && (c.alpha.x == 1.0 || c.alpha.x == -1.0);
         const bool neg = one && c.alpha.x < 0.0;
-        if (!c.ah) turn(c.a, XA);
-        if (c.bh) turn(c.b, XB);
+        if (!c.ah) turn16(c.a, XA, q, kq);
+        if (c.bh) turn16(c.b, XB, q, kq);
         // conjugation and alpha, each behind a wave-uniform branch
         if (c.ah) {
 #pragma unroll
