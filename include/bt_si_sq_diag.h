@@ -60,6 +60,13 @@ size_t bt_si_sq_diag_inverse_noalloc_max_bytes(void);
  * (NUL-terminated) and returns the length the full text needs. */
 size_t bt_si_sq_diag_schedule(const bt_desc* desc, char* out, size_t cap);
 
+/* Order in which the workgroups of one launch take the output tiles of its count
+ * products, given each product's number of tiles and its k (host arrays): entry
+ * product << 32 | tile, or all ones for a workgroup without work.  Pure host
+ * computation.  Writes at most cap entries and returns how many there are. */
+size_t bt_si_sq_diag_tile_order(int32_t count, const int32_t* tiles, const int32_t* k, uint64_t* out,
+                                size_t cap);
+
 #ifdef __cplusplus
 }
 #endif

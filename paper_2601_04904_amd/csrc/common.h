@@ -37,10 +37,13 @@ struct GemmOp {
     GemmTerm t[kMaxTerms];
 };
 
-// Tile order of a product launch: workgroup b computes tile (entry & mask) of
-// product (entry >> kTileBits); kNoTile: nothing to do.
-constexpr int kTileBits = 11;
-constexpr uint32_t kNoTile = 0xffffffffu;
+// Tile order of a product launch: workgroup b computes tile (low 32 bits of its entry)
+// of product (high 32 bits); kNoTile (no product has that number): nothing to do.
+typedef uint64_t TileEntry;
+constexpr TileEntry kNoTile = ~(TileEntry)0;
+__host__ __device__ inline TileEntry tile_entry(uint32_t product, uint32_t tile) {
+    return (TileEntry)product << 32 | tile;
+}
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  This maps dispatch index b of a grid of g workgroups to a logical

@@ -500,17 +500,17 @@ struct WaveTile<true, BM, BN> {
 // One workgroup computes a BM x BN complex tile of one product.
 template <bool MIXED, int BM, int BN>
 __global__ __launch_bounds__(kThreads)
-void zgemm_grouped(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ order) {
+void zgemm_grouped(const GemmOp* __restrict__ ops, const TileEntry* __restrict__ order) {
     typedef typename std::conditional<MIXED, float2, double2>::type CT;     // element in LDS
     __shared__ CT As[2][kBK][BM + 1];
     __shared__ CT Bs[2][kBK][BN + 1];
 
     // which tile of which product: from the launch's order, or all tiles of the only
     // product
-    const uint32_t at = order ? order[blockIdx.x] : (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    const TileEntry at = order ? order[blockIdx.x] : tile_entry(0, xcd_remap(blockIdx.x, gridDim.x));
     if (at == kNoTile) return;
-    const GemmOp* op = ops + (order ? at >> kTileBits : 0u);
-    const int local = (int)(order ? at & ((1u << kTileBits) - 1) : at);
+    const GemmOp* op = ops + (uint32_t)(at >> 32);
+    const int local = (int)(uint32_t)at;
     const int m = op->m, n = op->n, nterms = op->nterms;
     const int tm = local / op->tiles_n, tn = local - tm * op->tiles_n;
     const int i0 = tm * BM, j0 = tn * BN;
@@ -662,17 +662,17 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ 
 constexpr int kSmallWaves = 4;
 template <bool MIXED>
 __global__ __launch_bounds__(64 * kSmallWaves)
-void zgemm_small(const GemmOp* __restrict__ ops, const uint32_t* __restrict__ order) {
+void zgemm_small(const GemmOp* __restrict__ ops, const TileEntry* __restrict__ order) {
     union Work {
         Turn turn[kSmallWaves][2];
         double2 sum[kSmallWaves][4][64];
     };
     __shared__ Work L;
-    const uint32_t at = order ? order[blockIdx.x] : blockIdx.x;
+    const TileEntry at = order ? order[blockIdx.x] : tile_entry(0, blockIdx.x);
     if (at == kNoTile) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const OpRegs o(ops[order ? at >> kTileBits : 0u], lane);
-    const int tile = (int)(order ? at & ((1u << kTileBits) - 1) : at);
+    const OpRegs o(ops[(uint32_t)(at >> 32)], lane);
+    const int tile = (int)(uint32_t)at;
     const int m = o.head(offsetof(GemmOp, m) / 4), n = o.head(offsetof(GemmOp, n) / 4);
     const int tn = (n + 15) >> 4, ti = tile / tn;
     const int i0 = ti * 16, j0 = (tile - ti * tn) * 16;
@@ -714,7 +714,7 @@ int gemm_tiles_shape(int m, int n, int shape) {
 int gemm_tiles_n_shape(int n, int shape) { return (n + kShapes[shape].bn - 1) / kShapes[shape].bn; }
 
 template <bool MIXED>
-static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid, int shape, hipStream_t s) {
+static void launch_mixed(const GemmOp* d_ops, const TileEntry* d_order, int grid, int shape, hipStream_t s) {
     switch (shape) {
         case 0: hipLaunchKernelGGL((zgemm_grouped<MIXED, 32, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
         case 1: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
@@ -725,7 +725,7 @@ static void launch_mixed(const GemmOp* d_ops, const uint32_t* d_order, int grid,
 
 // d_order: the launch's tile order (grid entries, gemm_tile_order), or null for a
 // single product, whose tiles then are the grid.
-hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s) {
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     if (shape < 0 || shape > kSmallShape) return hipErrorInvalidValue;
     if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);

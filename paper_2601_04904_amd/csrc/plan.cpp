@@ -44,7 +44,7 @@
 #include <vector>
 
 namespace btsq {
-hipError_t launch_gemm_shape(const GemmOp* d_ops, const uint32_t* d_order, int grid, bool mixed, int shape, hipStream_t s);
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, hipStream_t s);
 int gemm_tiles_shape(int m, int n, int shape);
 int gemm_tiles_n_shape(int n, int shape);
 int gemm_shape_bm(int shape);
@@ -910,7 +910,7 @@ void gemm_work(const GemmOp* ops, int n, double& flops, double& bytes) {
 
 struct Program {
     std::vector<GemmOp> gemm;
-    std::vector<uint32_t> order;    // tile orders of the product launches
+    std::vector<TileEntry> order;   // tile orders of the product launches
     std::vector<InvJob> inv;
     std::vector<AddOp> add;
     std::vector<NormJob> norm;
@@ -1011,12 +1011,12 @@ int default_shape(int mixed, const long* tiles) {
 }
 
 // Whether kSmallShape may compute the product: its 32-bit byte offsets, 24-bit
-// index products and the tile number in an order entry.
+// index products; above 2048 tiles a product is not small (and none was measured).
 bool small_fits(const GemmOp& g) {
-    constexpr int kLd = 1 << 16;
+    constexpr int kLd = 1 << 16, kMaxTiles = 2048;
     auto ok = [](int ld) { return ld >= 1 && ld <= kLd; };
     if (g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc)) ||
-        gemm_tiles_shape(g.m, g.n, kSmallShape) > (1 << kTileBits))
+        gemm_tiles_shape(g.m, g.n, kSmallShape) > kMaxTiles)
         return false;
     for (int t = 0; t < g.nterms; ++t)
         if (g.t[t].k > kInvMaxDim || !ok(g.t[t].lda) || !ok(g.t[t].ldb)) return false;
@@ -1055,40 +1055,48 @@ int pick_shape(int mixed, int maxdim, const long* tiles) {
 // and neighbouring tiles (which share operand rows or columns) still meet in one
 // L2.  One contiguous run of all tiles per XCD left the XCDs that got the long
 // products working alone.
-void gemm_tile_order(const GemmOp* ops, int n, int shape, std::vector<uint32_t>& out) {
-    std::vector<std::pair<double, int>> by(n);
-    for (int i = 0; i < n; ++i) {
-        double k = 0;
-        for (int t = 0; t < ops[i].nterms; ++t) k += ops[i].t[t].k;
-        by[i] = {k, i};
-    }
-    std::stable_sort(by.begin(), by.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-    std::vector<uint32_t> queue[kNumXcd], cls;
+struct OrderItem {
+    double k;      // of the product, summed over its terms
+    int tiles;
+};
+void tile_order(const std::vector<OrderItem>& items, std::vector<TileEntry>& out) {
+    std::vector<uint32_t> by(items.size());
+    for (size_t i = 0; i < by.size(); ++i) by[i] = (uint32_t)i;
+    std::stable_sort(by.begin(), by.end(), [&](uint32_t x, uint32_t y) { return items[x].k > items[y].k; });
+    std::vector<TileEntry> queue[kNumXcd], cls;
     double load[kNumXcd] = {};
-    for (int i = 0; i < n;) {
-        const double k0 = by[i].first;
+    for (size_t i = 0; i < by.size();) {
+        const double k0 = items[by[i]].k;
         cls.clear();
-        for (; i < n && by[i].first >= 0.75 * k0; ++i) {
-            const int op = by[i].second, tiles = gemm_tiles_shape(ops[op].m, ops[op].n, shape);
-            for (int t = 0; t < tiles; ++t) cls.push_back((uint32_t)op << kTileBits | (uint32_t)t);
-        }
+        for (; i < by.size() && items[by[i]].k >= 0.75 * k0; ++i)
+            for (int t = 0; t < items[by[i]].tiles; ++t) cls.push_back(tile_entry(by[i], (uint32_t)t));
         // the XCDs with the least work so far take one tile more where it does not divide
-        int xcd[kNumXcd], size[kNumXcd];
+        int xcd[kNumXcd];
+        size_t size[kNumXcd];
         for (int x = 0; x < kNumXcd; ++x) xcd[x] = x;
         std::stable_sort(xcd, xcd + kNumXcd, [&](int x, int y) { return load[x] < load[y]; });
         for (int r = 0; r < kNumXcd; ++r)
-            size[xcd[r]] = (int)(cls.size() / kNumXcd) + (r < (int)(cls.size() % kNumXcd) ? 1 : 0);
+            size[xcd[r]] = cls.size() / kNumXcd + (r < (int)(cls.size() % kNumXcd) ? 1 : 0);
         size_t at = 0;
         for (int x = 0; x < kNumXcd; ++x) {
             queue[x].insert(queue[x].end(), cls.begin() + at, cls.begin() + at + size[x]);
             at += size[x];
-            load[x] += std::max(k0, 1.0) * size[x];
+            load[x] += std::max(k0, 1.0) * (double)size[x];
         }
     }
     size_t longest = 0;
     for (auto& q : queue) longest = std::max(longest, q.size());
     for (size_t i = 0; i < longest; ++i)
         for (auto& q : queue) out.push_back(i < q.size() ? q[i] : kNoTile);
+}
+
+void gemm_tile_order(const GemmOp* ops, int n, int shape, std::vector<TileEntry>& out) {
+    std::vector<OrderItem> items(n);
+    for (int i = 0; i < n; ++i) {
+        items[i] = {0.0, gemm_tiles_shape(ops[i].m, ops[i].n, shape)};
+        for (int t = 0; t < ops[i].nterms; ++t) items[i].k += ops[i].t[t].k;
+    }
+    tile_order(items, out);
 }
 
 void set_shape(Program& pg, Launch& L, int shape) {
@@ -1654,7 +1662,7 @@ hipError_t run_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c) {
 hipError_t enqueue_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c, hipStream_t main) {
     const Program& pg = c.prog;
     GemmOp* dg = reinterpret_cast<GemmOp*>(c.dev + c.off_gemm);
-    const uint32_t* dord = reinterpret_cast<const uint32_t*>(c.dev + c.off_order);
+    const TileEntry* dord = reinterpret_cast<const TileEntry*>(c.dev + c.off_order);
     InvJob* dj = reinterpret_cast<InvJob*>(c.dev + c.off_inv);
     AddOp* da = reinterpret_cast<AddOp*>(c.dev + c.off_add);
     NormJob* dn = reinterpret_cast<NormJob*>(c.dev + c.off_norm);
@@ -1737,7 +1745,7 @@ struct ProgLayout {
 ProgLayout program_layout(const Program& pg) {
     ProgLayout L;
     L.off_order = align256(pg.gemm.size() * sizeof(GemmOp));
-    L.off_inv = align256(L.off_order + pg.order.size() * sizeof(uint32_t));
+    L.off_inv = align256(L.off_order + pg.order.size() * sizeof(TileEntry));
     L.off_add = align256(L.off_inv + pg.inv.size() * sizeof(InvJob));
     L.off_norm = align256(L.off_add + pg.add.size() * sizeof(AddOp));
     L.off_frec = align256(L.off_norm + pg.norm.size() * sizeof(NormJob));
@@ -1845,7 +1853,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         char* stage = c->host.data();
         auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) memcpy(stage + off, src, bytes); };
         put(0, pg.gemm.data(), pg.gemm.size() * sizeof(GemmOp));
-        put(PL.off_order, pg.order.data(), pg.order.size() * sizeof(uint32_t));
+        put(PL.off_order, pg.order.data(), pg.order.size() * sizeof(TileEntry));
         put(PL.off_inv, pg.inv.data(), pg.inv.size() * sizeof(InvJob));
         put(PL.off_add, pg.add.data(), pg.add.size() * sizeof(AddOp));
         put(PL.off_norm, pg.norm.data(), pg.norm.size() * sizeof(NormJob));
@@ -2376,14 +2384,14 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     // room for the operations and, behind them, the longest tile order: 2^13 tiles of
     // 64 x 32 are at most 2^14 of 32 x 32, and the padding is below one per XCD
     const size_t ops_bytes = align256(kMaxOps * sizeof(GemmOp));
-    const size_t order_bytes = ((size_t)1 << kTClasses) * 2 * sizeof(uint32_t) + 64 * kNumXcd;
+    const size_t order_bytes = ((size_t)1 << kTClasses) * 2 * sizeof(TileEntry) + 64 * kNumXcd;
     e = hipMalloc(&dops, ops_bytes + order_bytes);
     if (e != hipSuccess) { hipGetLastError(); hipFree(buf); return set_err(nullptr, BT_ERR_OOM, "autotune: op list allocation failed"); }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&ev0);
     if (e == hipSuccess) e = hipEventCreate(&ev1);
     if (e == hipSuccess) e = hipMemsetAsync(buf, 0, 2 * in_bytes + out_bytes, s);
-    uint32_t* dorder = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(dops) + ops_bytes);
+    TileEntry* dorder = reinterpret_cast<TileEntry*>(reinterpret_cast<char*>(dops) + ops_bytes);
     const double2* A = reinterpret_cast<const double2*>(buf);
     const double2* B = reinterpret_cast<const double2*>(buf + in_bytes);
     double2* out = reinterpret_cast<double2*>(buf + 2 * in_bytes);
@@ -2391,7 +2399,7 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     for (auto& a : found) for (auto& b : a) for (auto& c : b) c = -1;
     std::string rep;
     std::vector<GemmOp> ops;
-    std::vector<uint32_t> order;
+    std::vector<TileEntry> order;
     for (int prec = 0; prec < 2 && e == hipSuccess; ++prec) {
         for (int mc = 1; mc < kMClasses && e == hipSuccess; ++mc) {
             const int m = 32 << mc;
@@ -2426,7 +2434,7 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
                     const int grid = (int)order.size();
                     e = hipMemcpyAsync(dops, ops.data(), ops.size() * sizeof(GemmOp), hipMemcpyHostToDevice, s);
                     if (e == hipSuccess)
-                        e = hipMemcpyAsync(dorder, order.data(), grid * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+                        e = hipMemcpyAsync(dorder, order.data(), grid * sizeof(TileEntry), hipMemcpyHostToDevice, s);
                     if (e == hipSuccess) e = hipStreamSynchronize(s);     // the lists are reused below
                     if (e == hipSuccess) e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, s);   // warm-up
                     if (e == hipSuccess) e = hipEventRecord(ev0, s);
@@ -2626,4 +2634,15 @@ extern "C" size_t bt_si_sq_diag_schedule(const bt_desc* desc, char* out, size_t 
         out[c] = 0;
     }
     return txt.size() + 1;
+}
+
+extern "C" size_t bt_si_sq_diag_tile_order(int32_t count, const int32_t* tiles, const int32_t* k, uint64_t* out,
+                                           size_t cap) {
+    if (count < 1 || !tiles || !k) return 0;
+    std::vector<OrderItem> items(count);
+    for (int i = 0; i < count; ++i) items[i] = {(double)k[i], tiles[i]};
+    std::vector<TileEntry> order;
+    tile_order(items, order);
+    if (out) std::copy(order.begin(), order.begin() + std::min(cap, order.size()), out);
+    return order.size();
 }

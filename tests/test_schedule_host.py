@@ -1,0 +1,33 @@
+"""What the host schedules for the GPU, checked without one."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2601_04904_amd import _lib
+
+
+def tile_order(tiles, k):
+    """(product, tile) pairs of a launch's order, padding left out."""
+    tiles, k = np.ascontiguousarray(tiles, np.int32), np.ascontiguousarray(k, np.int32)
+    i32, u64 = C.POINTER(C.c_int32), C.POINTER(C.c_uint64)
+    args = (len(tiles), tiles.ctypes.data_as(i32), k.ctypes.data_as(i32))
+    n = _lib.lib().bt_si_sq_diag_tile_order(*args, None, 0)
+    out = np.empty(n, np.uint64)
+    assert _lib.lib().bt_si_sq_diag_tile_order(*args, out.ctypes.data_as(u64), n) == n
+    out = out[out != np.uint64(2 ** 64 - 1)]
+    return (out >> np.uint64(32)).astype(np.int64), (out & np.uint64(2 ** 32 - 1)).astype(np.int64)
+
+
+@pytest.mark.parametrize("count,last", [(1, 1), (7, 2049), (130, 5), (2 ** 21 + 3, 1)])
+def test_every_tile_of_a_launch_once(count, last):
+    """Every tile of every product exactly once: products past 2^21 in one launch, and a
+    product of more than 2^11 tiles."""
+    tiles = np.ones(count, np.int64)
+    tiles[-1] = last
+    p, t = tile_order(tiles, 8 + 100 * (np.arange(count) % 3))
+    assert len(p) == tiles.sum()
+    at = np.lexsort((t, p))
+    first = np.concatenate([[0], np.cumsum(tiles)[:-1]])
+    assert np.array_equal(p[at], np.repeat(np.arange(count), tiles))
+    assert np.array_equal(t[at], np.arange(len(p)) - first[p[at]])
