@@ -74,7 +74,7 @@ __device__ void fused_tile(const GemmOp& op, int tile, int lane, Turn& XA, Turn&
         for (int r = 0; r < 4; ++r) cv[r] = load16(rc, (__mul24(i0 + kq + 4 * r, ldc) + j0 + q) * 16);
     }
     v4d re, im;
-    tile16_sum<1, false>(o, m, n, i0, j0, 0, lane, XA, XB, re, im);
+    tile16_sum(o, m, n, i0, j0, lane, XA, XB, re, im);
     const double2 beta = op_beta(o);
     const int ldd = o.head(offsetof(GemmOp, ldd) / 4);
     const __amdgpu_buffer_rsrc_t rd = fused_rsrc(op_d(o), m, n, ldd);

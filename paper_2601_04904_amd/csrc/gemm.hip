@@ -20,7 +20,7 @@
 // around every stage, which halves the rate of the 16x16x4 instruction (36
 // against 77.5 TFLOP/s in a loop of it alone).
 //
-// Mixed path (all but the 16 x 16 tiles): complex arithmetic on real MFMA by a 2 x 2 real embedding.  A
+// Mixed path: complex arithmetic on real MFMA by a 2 x 2 real embedding.  A
 // complex m x k matrix A stored as interleaved (re, im) is read as the real
 // m x 2k matrix A', and op(B) (k x n complex) is expanded on the fly into the
 // real 2k x 2n matrix
@@ -36,8 +36,9 @@ namespace btsq {
 constexpr int kBK = 16;          // complex k per LDS stage
 constexpr int kThreads = 256;    // 4 waves, 2 x 2 over the tile
 
+// a b, with the same roundings in every kernel
 __device__ inline double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 
 // Global pointer in the global address space (the C operand's loads).
@@ -76,6 +77,15 @@ struct StageFlags {
     double2 alpha;
 };
 
+__device__ inline StageFlags term_flags(const GemmTerm& T) {
+    StageFlags f;
+    f.ah = T.flags & kTermAH;
+    f.bh = T.flags & kTermBH;
+    f.alpha = T.alpha;
+    f.akind = T.alpha.y != 0.0 ? 0 : T.alpha.x == 1.0 ? 1 : T.alpha.x == -1.0 ? 2 : 0;
+    return f;
+}
+
 // Addressing of one thread's loads for one product term, fixed over all k
 // stages of the term: the byte offset of each load at k = 0 (kOOB when its
 // A row or B column lies outside the matrix) and the bytes per unit of k.
@@ -106,10 +116,7 @@ template <int BM, int BN>
 __device__ inline void term_setup(const GemmTerm& T, int m, int n, int i0, int j0, int tid,
                                   TermAddr<BM, BN>& ta) {
     const bool ah = T.flags & kTermAH, bh = T.flags & kTermBH;
-    ta.f.ah = ah;
-    ta.f.bh = bh;
-    ta.f.alpha = T.alpha;
-    ta.f.akind = T.alpha.y != 0.0 ? 0 : T.alpha.x == 1.0 ? 1 : T.alpha.x == -1.0 ? 2 : 0;
+    ta.f = term_flags(T);
     ta.ska = (ah ? T.lda : 1) * 16;
     ta.skb = (bh ? 1 : T.ldb) * 16;
     ta.ra = ah ? operand_rsrc(T.A, T.k, m, T.lda) : operand_rsrc(T.A, m, T.k, T.lda);
@@ -215,20 +222,21 @@ __device__ inline void scale_stage(Stage<BM, BN>& st) {
     }
 }
 
-// A stage to LDS (out-of-range values are already zero), mixed path.
-// Conjugation and alpha = -1 are sign flips with wave-uniform masks.
-template <int BM, int BN>
-__device__ inline void store_stage_mixed(int tid, const Stage<BM, BN>& st, float2 (*As)[BM + 1], float2 (*Bs)[BN + 1]) {
+// A stage to LDS (out-of-range values are already zero), rounded to FP32 in the mixed
+// path.  Conjugation and alpha = -1 are sign flips with wave-uniform masks.
+__device__ inline void round_to(float2& to, double2 v) { to = make_float2((float)v.x, (float)v.y); }
+__device__ inline void round_to(double2& to, double2 v) { to = v; }
+template <int BM, int BN, class CT>
+__device__ inline void store_stage(int tid, const Stage<BM, BN>& st, CT (*As)[BM + 1], CT (*Bs)[BN + 1]) {
     constexpr unsigned long long kSign = 0x8000000000000000ull;
     const StageFlags& f = st.f;
     const bool neg = f.akind == 2;
-    auto cvt = [](double2 v) { return make_float2((float)v.x, (float)v.y); };
 #pragma unroll
     for (int e = 0; e < Stage<BM, BN>::NA; ++e) {
         const int x = tid + kThreads * e;
         double2 v = st.ra[e];
         v.y = flip_sign(v.y, f.ah ? kSign : 0ull);
-        As[a_p<BM>(f.ah, x)][a_i<BM>(f.ah, x)] = cvt(v);
+        round_to(As[a_p<BM>(f.ah, x)][a_i<BM>(f.ah, x)], v);
     }
 #pragma unroll
     for (int e = 0; e < Stage<BM, BN>::NB; ++e) {
@@ -236,7 +244,7 @@ __device__ inline void store_stage_mixed(int tid, const Stage<BM, BN>& st, float
         double2 v = st.rb[e];
         v.x = flip_sign(v.x, neg ? kSign : 0ull);
         v.y = flip_sign(v.y, f.bh != neg ? kSign : 0ull);
-        Bs[b_p<BN>(f.bh, x)][b_j<BN>(f.bh, x)] = cvt(v);
+        round_to(Bs[b_p<BN>(f.bh, x)][b_j<BN>(f.bh, x)], v);
     }
 }
 
@@ -338,8 +346,9 @@ struct WaveTile<false, BM, BN> {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const double2 c = cv[a][b][r];
-                    re[a][b][r] = beta.x * c.x - beta.y * c.y;
-                    im[a][b][r] = beta.x * c.y + beta.y * c.x;
+                    const double2 v = cmul(beta, c);
+                    re[a][b][r] = v.x;
+                    im[a][b][r] = v.y;
                 }
     }
 
@@ -489,8 +498,8 @@ struct WaveTile<true, BM, BN> {
                     const int col = j0 + ((ni * 16 + cq) >> 1);
                     double v = (double)acc[g][ni][r];
                     if (op->C) {
-                        const double2 c = cv[g][ni][r];
-                        v += d ? (beta.x * c.y + beta.y * c.x) : (beta.x * c.x - beta.y * c.y);
+                        const double2 c = cmul(beta, cv[g][ni][r]);
+                        v += d ? c.y : c.x;
                     }
                     if (row < m && col < n) D[2 * ((size_t)row * ldd + col) + d] = v;
                 }
@@ -543,7 +552,7 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const TileEntry* __restrict__
     constexpr int NL = Stage<BM, BN>::NA + Stage<BM, BN>::NB;
 
     if constexpr (MIXED) {
-        if (cur) store_stage_mixed<BM, BN>(tid, st[0], As[0], Bs[0]);
+        if (cur) store_stage<BM, BN>(tid, st[0], As[0], Bs[0]);
         __syncthreads();
         // one stage: X = register set in flight (the next stage), Y = free set,
         // X - 1 the parity of the LDS buffer multiplied
@@ -559,7 +568,7 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const TileEntry* __restrict__
             // unconditional like the loads: without a next stage st[X] holds
             // zeros from kOOB loads, stored to the buffer no later stage reads
             scale_stage<BM, BN>(st[X]);
-            store_stage_mixed<BM, BN>(tid, st[X], As[buf ^ 1], Bs[buf ^ 1]);
+            store_stage<BM, BN>(tid, st[X], As[buf ^ 1], Bs[buf ^ 1]);
             __syncthreads();
             cur = fly;
             fly = fe.lim >= 0;
@@ -652,52 +661,236 @@ void zgemm_grouped(const GemmOp* __restrict__ ops, const TileEntry* __restrict__
 }
 
 // Launches with at most about one larger tile per CU (kSmallShape): one 16 x 16 tile per
-// workgroup, its 4 waves each taking every fourth 16-deep chunk of k, the sums added
-// through LDS.  Four times the workgroups of 32 x 32 tiles and no barrier before the
-// end; what is left is the latency of the launch, of the descriptor and of the first
-// loads.  Against 32 x 32 tiles: 1 product of 32 4.0 -> 3.3 us, of 128 8.0 -> 4.5 us,
-// 3 of 256 14.0 -> 12.2 us (mixed, where the sums of the waves are added in FP64: 5.1 ->
-// 3.2, 9.3 -> 4.2, 15.5 -> 9.6 us); with many tiles per CU the operands are read too often
-// (6 of 512: 112 us in 64 x 32 tiles, 131 us here).
-constexpr int kSmallWaves = 4;
-template <bool MIXED>
-__global__ __launch_bounds__(64 * kSmallWaves)
+// workgroup, four times the workgroups of 32 x 32 tiles.  What is left is the latency of
+// the launch, of the descriptor (read in one go into the lanes of a wave) and of the first
+// loads, then the chain of sums of one entry.  The waves share the tile's entries and
+// not its k: v_mfma_f64_4x4x4 with A replicated over its four blocks is a 4-row x
+// 16-column x 4-k product (A[lane%4][lane/16], B[lane/16][lane%16], D row lane/16,
+// column lane%16), a quarter of the chain of the 16x16x4 instruction at the same rate, and
+// both round as an ascending chain of fused multiply-adds (measured: no difference in
+// 512000 sums of 64), so a product has the same bits in every shape and does not depend
+// on what else is in its launch.  Mixed: the real embedding of the larger tiles, two waves
+// of 8 columns.
+// Against 32 x 32 tiles, us: 1 product of 32 4.1 -> 3.4, of 64 5.6 -> 4.0, of 128 8.3 ->
+// 5.1, of 256 13.4 -> 7.7, 3 of 192 11.2 -> 9.4 (mixed 5.3 -> 3.5, 6.7 -> 4.3, 9.5 -> 5.6,
+// 15.4 -> 8.6, 12.6 -> 9.0).  A wave per part of k, as an order of its own, would take 4.7
+// and 6.9 us for one product of 128 and 256.
+//
+// G: chunks of kBK k's held in LDS at a time, all of whose loads are issued: 8, or as many
+// as the longest term of the launch fills (8 for one product of 32: 4.2 us).
+template <bool MIXED, int G>
+__global__ __launch_bounds__(kThreads)
 void zgemm_small(const GemmOp* __restrict__ ops, const TileEntry* __restrict__ order) {
-    union Work {
-        Turn turn[kSmallWaves][2];
-        double2 sum[kSmallWaves][4][64];
-    };
-    __shared__ Work L;
+    typedef typename std::conditional<MIXED, float2, double2>::type CT;
+    __shared__ CT As[G][kBK][17], Bs[G][kBK][17];
     const TileEntry at = order ? order[blockIdx.x] : tile_entry(0, blockIdx.x);
     if (at == kNoTile) return;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const OpRegs o(ops[(uint32_t)(at >> 32)], lane);
     const int tile = (int)(uint32_t)at;
     const int m = o.head(offsetof(GemmOp, m) / 4), n = o.head(offsetof(GemmOp, n) / 4);
+    const int nt = o.head(offsetof(GemmOp, nterms) / 4);
     const int tn = (n + 15) >> 4, ti = tile / tn;
     const int i0 = ti * 16, j0 = (tile - ti * tn) * 16;
-    const int q = lane & 15, row = i0 + tile16_row<MIXED>(lane, wave);     // of the entry this lane writes
+
+    // this lane's entries of the tile: FP64 one of the wave's 4 rows, mixed 4 rows of one
+    // component of a column of waves 0 and 1
+    constexpr int NE = MIXED ? 4 : 1;
+    const bool mine = !MIXED || wave < 2;
+    const int row = i0 + (MIXED ? 4 * (lane >> 4) : 4 * wave + (lane >> 4));
+    const int col = j0 + (MIXED ? 8 * wave + ((lane & 15) >> 1) : lane & 15);
     double2* C = op_c(o);
-    double2 cv = make_double2(0.0, 0.0);
-    if (C) {
+    double2 cv[NE];
+    if (C && mine) {
         const int ldc = o.head(offsetof(GemmOp, ldc) / 4);
-        cv = load16(fused_rsrc(C, m, n, ldc), (__mul24(row, ldc) + j0 + q) * 16);
-    }
-    typename Tile16Acc<MIXED>::type re, im;
-    tile16_sum<kSmallWaves, MIXED>(o, m, n, i0, j0, wave, lane, L.turn[wave][0], L.turn[wave][1], re, im);
-    __syncthreads();                     // the sums take the place of the operands
 #pragma unroll
-    for (int r = 0; r < 4; ++r) L.sum[wave][r][lane] = make_double2(re[r], im[r]);
-    __syncthreads();
-    double2 v = make_double2(0.0, 0.0);
-    if (C) cfma(v, op_beta(o), cv);
-#pragma unroll
-    for (int w = 0; w < kSmallWaves; ++w) {
-        v.x += L.sum[w][wave][lane].x;
-        v.y += L.sum[w][wave][lane].y;
+        for (int r = 0; r < NE; ++r)
+            cv[r] = load16(fused_rsrc(C, m, n, ldc), (__mul24(row + r, ldc) + col) * 16);
     }
+
+    // A step is up to G chunks of one term, multiplied from LDS while the loads of the
+    // next one are in flight.
+    double2 av[G], bv[G];
+    TermAddr<16, 16> ta;
+    int s = -1, lim = -1, soa = 0, sob = 0;      // term, largest k in it from the step's first on, scalar offsets
     const int ldd = o.head(offsetof(GemmOp, ldd) / 4);
-    if (j0 + q < n) store16(fused_rsrc(op_d(o), m, n, ldd), (__mul24(row, ldd) + j0 + q) * 16, v);
+    const __amdgpu_buffer_rsrc_t rd = fused_rsrc(op_d(o), m, n, ldd);
+    ta.ra = ta.rb = rd;                          // (without any term: nothing is read through them)
+    ta.va[0] = ta.vb[0] = kOOB;
+    ta.ska = ta.skb = 0;
+    ta.f = StageFlags{};
+    // Loads the next step; returns how many chunks it has.  Entries
+    // past k, and everything past the last term, are switched off by their offset: the
+    // loads are unconditional, since a register loaded in a branch is waited for at its
+    // end.
+    auto load = [&]() {
+        lim -= G * kBK;
+        soa += G * kBK * ta.ska;
+        sob += G * kBK * ta.skb;
+        if (lim < 0) {
+            soa = sob = 0;
+            while (s < nt && ++s < nt) {
+                GemmTerm T;
+                T.k = o.term(s, offsetof(GemmTerm, k) / 4);
+                if (T.k <= 0) continue;
+                T.A = OpRegs::ptr(o.term(s, 0), o.term(s, 1));
+                T.B = OpRegs::ptr(o.term(s, 2), o.term(s, 3));
+                T.lda = o.term(s, offsetof(GemmTerm, lda) / 4);
+                T.ldb = o.term(s, offsetof(GemmTerm, ldb) / 4);
+                T.flags = o.term(s, offsetof(GemmTerm, flags) / 4);
+                constexpr int kAl = offsetof(GemmTerm, alpha) / 4;
+                T.alpha = make_double2(OpRegs::real(o.term(s, kAl), o.term(s, kAl + 1)),
+                                       OpRegs::real(o.term(s, kAl + 2), o.term(s, kAl + 3)));
+                term_setup<16, 16>(T, m, n, i0, j0, tid, ta);
+                lim = T.k - 1;
+                break;
+            }
+        }
+        const int pa = a_p<16>(ta.f.ah, tid), pb = b_p<16>(ta.f.bh, tid);
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+            const int left = lim - c * kBK;
+            av[c] = load_b128(ta.ra, ta.va[0] | ((unsigned)(left - pa) & kOOB),
+                                   __builtin_amdgcn_readfirstlane(left < 0 ? 0 : soa + c * kBK * ta.ska));
+            bv[c] = load_b128(ta.rb, ta.vb[0] | ((unsigned)(left - pb) & kOOB),
+                                   __builtin_amdgcn_readfirstlane(left < 0 ? 0 : sob + c * kBK * ta.skb));
+        }
+        return lim < 0 ? 0 : min(lim / kBK + 1, G);
+    };
+    // Operands as they are in memory but for conjugation and a general alpha; alpha = -1 is
+    // a change of the accumulators' sign.
+    unsigned pa = 0, pb = 0;                     // this thread's places in a chunk of As, Bs
+    int layout = -1;
+    bool neg = false, neg_lds = false;           // sign of the accumulators / of the step in LDS
+    auto to_lds = [&](int g) {
+        const int want = (ta.f.ah ? 1 : 0) | (ta.f.bh ? 2 : 0);
+        if (want != layout) {
+            layout = want;
+            pa = (a_p<16>(ta.f.ah, tid) * 17 + a_i<16>(ta.f.ah, tid)) * sizeof(CT);
+            pb = (b_p<16>(ta.f.bh, tid) * 17 + b_j<16>(ta.f.bh, tid)) * sizeof(CT);
+        }
+        neg_lds = ta.f.akind == 2;
+#pragma unroll
+        for (int c = 0; c < G; c += 2) {
+            if (c >= 2 && c >= g) continue;
+            Stage<16, 16> x[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                // not before here: earlier, it would wait for the loads
+                asm volatile("" : "+v"(av[c + e].x), "+v"(av[c + e].y), "+v"(bv[c + e].x), "+v"(bv[c + e].y));
+                x[e].ra[0] = av[c + e];
+                x[e].rb[0] = bv[c + e];
+                x[e].f = ta.f;
+            }
+            if (want != 0 || ta.f.akind == 0) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    scale_stage<16, 16>(x[e]);
+                    conj_stage<16, 16>(x[e]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                round_to(*reinterpret_cast<CT*>(reinterpret_cast<char*>(As[c + e]) + pa), x[e].ra[0]);
+                round_to(*reinterpret_cast<CT*>(reinterpret_cast<char*>(Bs[c + e]) + pb), x[e].rb[0]);
+            }
+        }
+    };
+
+    // accumulators: re, im of the lane's entry, or (mixed) its four entries' component
+    double re = 0.0, im = 0.0;
+    v4f acc = {};
+    if constexpr (!MIXED) {
+        if (C) {
+            const double2 v = cmul(op_beta(o), cv[0]);
+            re = v.x;
+            im = v.y;
+        }
+    }
+    auto negate = [&]() {
+        re = -re;
+        im = -im;
+        if constexpr (MIXED) acc = -acc;
+    };
+    // A chunk's entries are read while the one before is multiplied (past g: whatever is
+    // there, not used).  KS instructions of 4 real or (mixed) 2 complex k's.
+    auto multiply = [&](int g) {
+        constexpr int KS = MIXED ? kBK / 2 : kBK / 4;
+        typedef typename std::conditional<MIXED, float, double2>::type Entry;
+        Entry fa[2][KS], fb[2][KS];
+        const int cA = (lane >> 4) & 1, d = lane & 1;          // mixed: as in the larger tiles
+        const int sign = cA == 1 && d == 0 ? (int)0x80000000u : 0;
+        auto read = [&](int c) {
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) {
+                if constexpr (MIXED) {
+                    const int p = 2 * kk + (lane >> 5);
+                    fa[c & 1][kk] = reinterpret_cast<const float*>(&As[c][p][lane & 15])[cA];
+                    fb[c & 1][kk] = reinterpret_cast<const float*>(&Bs[c][p][8 * wave + ((lane & 15) >> 1)])[cA ^ d];
+                } else {
+                    fa[c & 1][kk] = As[c][4 * kk + (lane >> 4)][4 * wave + (lane & 3)];
+                    fb[c & 1][kk] = Bs[c][4 * kk + (lane >> 4)][lane & 15];
+                }
+            }
+        };
+        if (!mine) return;
+        read(0);
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+            if (c < g) {
+                if (c + 1 < G) read(c + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk) {
+                    const Entry a = fa[c & 1][kk], b = fb[c & 1][kk];
+                    if constexpr (MIXED) {
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, __int_as_float(__float_as_int(b) ^ sign), acc, 0, 0, 0);
+                    } else {
+                        re = __builtin_amdgcn_mfma_f64_4x4x4f64(a.x, b.x, re, 0, 0, 0);
+                        im = __builtin_amdgcn_mfma_f64_4x4x4f64(a.x, b.y, im, 0, 0, 0);
+                        re = __builtin_amdgcn_mfma_f64_4x4x4f64(a.y, b.y, re, 0, 0, 1);
+                        im = __builtin_amdgcn_mfma_f64_4x4x4f64(a.y, b.x, im, 0, 0, 0);
+                    }
+                }
+            }
+        }
+    };
+    int cur = load();
+    to_lds(cur);
+    __syncthreads();
+    while (cur > 0) {
+        if (neg != neg_lds) {
+            neg = neg_lds;
+            negate();
+        }
+        const int next = load();
+        multiply(cur);
+        __syncthreads();
+        if (next > 0) {
+            to_lds(next);
+            __syncthreads();
+        }
+        cur = next;
+    }
+    if (neg) negate();
+
+    if constexpr (MIXED) {
+        if (mine && col < n) {
+            const int d = lane & 1;
+            const double2 beta = op_beta(o);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double v = (double)acc[r];
+                if (C) {
+                    const double2 c = cmul(beta, cv[r]);
+                    v += d ? c.y : c.x;
+                }
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rd, (__mul24(row + r, ldd) + col) * 16 + 8 * d, 0, 0);
+            }
+        }
+    } else {
+        if (col < n) store16(rd, (__mul24(row, ldd) + col) * 16, make_double2(re, im));
+    }
 }
 
 // Tile shapes of the grouped product (complex rows x complex columns).
@@ -714,22 +907,27 @@ int gemm_tiles_shape(int m, int n, int shape) {
 int gemm_tiles_n_shape(int n, int shape) { return (n + kShapes[shape].bn - 1) / kShapes[shape].bn; }
 
 template <bool MIXED>
-static void launch_mixed(const GemmOp* d_ops, const TileEntry* d_order, int grid, int shape, hipStream_t s) {
+static void launch_mixed(const GemmOp* d_ops, const TileEntry* d_order, int grid, int shape, int maxk, hipStream_t s) {
     switch (shape) {
         case 0: hipLaunchKernelGGL((zgemm_grouped<MIXED, 32, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
         case 1: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 32>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
-        case kSmallShape: hipLaunchKernelGGL(zgemm_small<MIXED>, dim3(grid), dim3(64 * kSmallWaves), 0, s, d_ops, d_order); break;
+        case kSmallShape:
+            if (maxk <= 2 * kBK) hipLaunchKernelGGL((zgemm_small<MIXED, 2>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order);
+            else if (maxk <= 4 * kBK) hipLaunchKernelGGL((zgemm_small<MIXED, 4>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order);
+            else hipLaunchKernelGGL((zgemm_small<MIXED, 8>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order);
+            break;
         default: hipLaunchKernelGGL((zgemm_grouped<MIXED, 64, 64>), dim3(grid), dim3(kThreads), 0, s, d_ops, d_order); break;
     }
 }
 
 // d_order: the launch's tile order (grid entries, gemm_tile_order), or null for a
-// single product, whose tiles then are the grid.
-hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, hipStream_t s) {
+// single product, whose tiles then are the grid.  maxk: the largest k of a term.
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, int maxk,
+                             hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     if (shape < 0 || shape > kSmallShape) return hipErrorInvalidValue;
-    if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, s);
-    else launch_mixed<false>(d_ops, d_order, grid, shape, s);
+    if (mixed) launch_mixed<true>(d_ops, d_order, grid, shape, maxk, s);
+    else launch_mixed<false>(d_ops, d_order, grid, shape, maxk, s);
     return hipGetLastError();
 }
 

@@ -44,7 +44,8 @@
 #include <vector>
 
 namespace btsq {
-hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, hipStream_t s);
+hipError_t launch_gemm_shape(const GemmOp* d_ops, const TileEntry* d_order, int grid, bool mixed, int shape, int maxk,
+                             hipStream_t s);
 int gemm_tiles_shape(int m, int n, int shape);
 int gemm_tiles_n_shape(int n, int shape);
 int gemm_shape_bm(int shape);
@@ -885,6 +886,7 @@ struct Launch {
     double flops = 0; // algorithmic work of the launch
     double bytes = 0;
     int shape = 1;    // gemm: tile shape (gemm_shape_bm / gemm_shape_bn)
+    int maxk = 0;     // gemm: largest k of a term
     int cls = 0;      // stream class
     int level = 0;
     int wait_level = -1;  // wait for the other stream up to this level
@@ -983,27 +985,29 @@ int log2_class(long v, int lo, int hi) {
 // a last tile to themselves (3 products of 512: 62, 76 and 73 us) and the
 // large one when there are many rounds (32 products: 649, 529 and 493 us).
 //
-// The 16 x 16 tiles of kSmallShape take 5.6 r + 4 on the same scale and are given
-// 6.5, since the fit is 10% low past five rounds.  They win while the launch has up
-// to about one 32 x 32 tile per CU, and where the outputs are so narrow that the
-// larger tiles are mostly padding: 1 product of 128: 8.0 (32 x 32) and 4.5 us, 3 of
-// 256: 14.0 and 12.2, 4 of 256: 14.3 and 14.2, 2 of 384: 30.1 (64 x 32) and 27.1;
-// but 3 of 384: 32.1 and 36.2, 2 of 512: 42.6 and 48.1.
+// The 16 x 16 tiles of kSmallShape take 8.3 r + 4 on the same scale, up to
+// kSmallRounds of them.  They win while there are few for each CU, whose waves then
+// have a quarter of the chain each: 1 product of 128 5.1 (8.3 in 32 x 32), 6 of 128 6.5
+// (8.4), 1 of 256 7.7 (13.4), 3 of 192 9.4 (11.2); but 6 of 192 16.6 (11.6), 3 of 256
+// 16.4 (14.3).  Past three rounds the operands are read too often (16 of 256: 71.7, 40.5
+// in 64 x 32).
 //
-// Mixed, on the same scale: 16 x 16 tiles take 4 r + 4 and 32 x 32 tiles 11 r + 16
-// (1 product of 128: 4.2 and 9.3 us, 4 of 256: 11.6 and 15.8, 2 of 512: 34.9 and
-// 38.2, 3 of 512: 49.8 and 49.2).
+// Mixed, on the same scale: 16 x 16 tiles take 5.3 r + 11 and 32 x 32 tiles 11 r + 16
+// (1 product of 128: 5.6 and 9.5 us, 3 of 256: 13.3 and 15.6, 6 of 192: 15.8 and 13.0).
+//
+// Every shape gives a product the same bits, so the choice may look at the whole launch.
+constexpr long kSmallRounds = 3;
 int default_shape(int mixed, const long* tiles) {
     auto rounds = [](long t) { return (t + 255) / 256; };
+    const bool small = tiles[kSmallShape] >= 0 && rounds(tiles[kSmallShape]) <= kSmallRounds;
     if (mixed) {
-        if (tiles[kSmallShape] >= 0 && 4 * rounds(tiles[kSmallShape]) + 4 < 11 * rounds(tiles[0]) + 16) return kSmallShape;
+        if (small && 5.3 * rounds(tiles[kSmallShape]) + 11 < 11 * rounds(tiles[0]) + 16) return kSmallShape;
         return tiles[1] < 512 ? 0 : 1;
     }
-    constexpr double kPerTile[kGemmShapes + 1] = {20.5, 33.0, 61.5, 6.5}, kFixed[kGemmShapes + 1] = {4.0, 10.0, 16.0, 4.0};
+    constexpr double kPerTile[kGemmShapes + 1] = {20.5, 33.0, 61.5, 8.3}, kFixed[kGemmShapes + 1] = {4.0, 10.0, 16.0, 4.0};
     int best = 0;
     double tb = 0.0;
-    for (int sh = 0; sh <= kSmallShape; ++sh) {
-        if (sh == kSmallShape && tiles[sh] < 0) break;
+    for (int sh = 0; sh <= (small ? kSmallShape : kGemmShapes - 1); ++sh) {
         const double t = kPerTile[sh] * (double)rounds(tiles[sh]) + kFixed[sh];
         if (sh == 0 || t < tb) { best = sh; tb = t; }
     }
@@ -1011,13 +1015,11 @@ int default_shape(int mixed, const long* tiles) {
 }
 
 // Whether kSmallShape may compute the product: its 32-bit byte offsets, 24-bit
-// index products; above 2048 tiles a product is not small (and none was measured).
+// index products.
 bool small_fits(const GemmOp& g) {
-    constexpr int kLd = 1 << 16, kMaxTiles = 2048;
+    constexpr int kLd = 1 << 16;
     auto ok = [](int ld) { return ld >= 1 && ld <= kLd; };
-    if (g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc)) ||
-        gemm_tiles_shape(g.m, g.n, kSmallShape) > kMaxTiles)
-        return false;
+    if (g.m > kInvMaxDim || g.n > kInvMaxDim || !ok(g.ldd) || (g.C && !ok(g.ldc))) return false;
     for (int t = 0; t < g.nterms; ++t)
         if (g.t[t].k > kInvMaxDim || !ok(g.t[t].lda) || !ok(g.t[t].ldb)) return false;
     return true;
@@ -1117,6 +1119,7 @@ void assign_shape(Program& pg, Launch& L) {
     for (int i = 0; i < L.count; ++i) {
         const GemmOp& g = pg.gemm[L.off + i];
         maxdim = std::max(maxdim, std::max(g.m, g.n));
+        for (int t = 0; t < g.nterms; ++t) L.maxk = std::max(L.maxk, (int)g.t[t].k);
     }
     set_shape(pg, L, pick_shape(L.mixed, maxdim, tiles));
 }
@@ -1692,7 +1695,7 @@ hipError_t enqueue_program(bt_si_sq_plan* h, bt_si_sq_plan::Cached& c, hipStream
             if (ea) hipEventRecord(ea, s);
         }
         switch (L.type) {
-            case 0: e = launch_gemm_shape(dg + L.off, dord + L.order_off, L.tiles, L.mixed != 0, L.shape, s); break;
+            case 0: e = launch_gemm_shape(dg + L.off, dord + L.order_off, L.tiles, L.mixed != 0, L.shape, L.maxk, s); break;
             case 4: e = launch_add(da + L.off, L.count, L.maxelems, s); break;
             case 5: e = launch_norms(dn + L.off, L.count, s); break;
             case 6: e = launch_inv_step(dj + L.off, L.count, L.maxd, L.panel, L.tiles, h->status, s); break;
@@ -2436,11 +2439,11 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
                     if (e == hipSuccess)
                         e = hipMemcpyAsync(dorder, order.data(), grid * sizeof(TileEntry), hipMemcpyHostToDevice, s);
                     if (e == hipSuccess) e = hipStreamSynchronize(s);     // the lists are reused below
-                    if (e == hipSuccess) e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, s);   // warm-up
+                    if (e == hipSuccess) e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, m, s);   // warm-up
                     if (e == hipSuccess) e = hipEventRecord(ev0, s);
                     constexpr int kReps = 3;
                     for (int r = 0; r < kReps && e == hipSuccess; ++r)
-                        e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, s);
+                        e = launch_gemm_shape(dops, dorder, grid, prec != 0, sh, m, s);
                     if (e == hipSuccess) e = hipEventRecord(ev1, s);
                     if (e == hipSuccess) e = hipEventSynchronize(ev1);
                     if (e == hipSuccess) e = hipEventElapsedTime(&ms[sh], ev0, ev1);
@@ -2533,7 +2536,7 @@ bt_status bt_si_sq_diag_gemm(int32_t m, int32_t n, int32_t k,
     hipError_t e = hipMalloc(&dop, sizeof g);
     if (e != hipSuccess) return hip_err(nullptr, e, "hipMalloc");
     e = hipMemcpyAsync(dop, &g, sizeof g, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_gemm_shape(dop, nullptr, gemm_tiles_shape(m, n, shape), mixed != 0, shape, s);
+    if (e == hipSuccess) e = launch_gemm_shape(dop, nullptr, gemm_tiles_shape(m, n, shape), mixed != 0, shape, k, s);
     hipError_t e2 = hipStreamSynchronize(s);
     hipFree(dop);
     if (e != hipSuccess) return hip_err(nullptr, e, "diag_gemm launch");

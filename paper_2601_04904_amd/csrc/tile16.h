@@ -1,7 +1,7 @@
-// A 16 x 16 tile of a grouped product by one wave, shared by the fused
-// small-instance kernel and the small-launch product kernel: operands go from
-// memory to the layout of v_mfma_f64_16x16x4 (v_mfma_f32_16x16x4f32, which has the
-// same operand layout, for products in complex64) without workgroup barriers.
+// Descriptors in lane registers and buffer addressing of 16 x 16 tiles, shared by the
+// fused small-instance kernel and the small-launch product kernel, and the fused
+// kernel's tile: one wave's, operands going from memory to the layout of
+// v_mfma_f64_16x16x4 without workgroup barriers.
 #pragma once
 #include "gauss.h"
 #include <cstddef>
@@ -24,7 +24,8 @@ struct OpRegs {
     __device__ inline int term(int s, int f) const {
         constexpr int kFirst = offsetof(GemmOp, t) / 4, kLen = sizeof(GemmTerm) / 4;
         const int i = kFirst + kLen * s + f;
-        return i < 64 ? lane_of(w0, i) : lane_of(w1, i - 64);
+        const int a = lane_of(w0, i & 63), b = lane_of(w1, i & 63);    // both, so that there is no branch
+        return i < 64 ? a : b;
     }
     static __device__ inline double real(int lo, int hi) {
         return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
@@ -45,6 +46,7 @@ __device__ inline __amdgpu_buffer_rsrc_t fused_rsrc(double2* base, int rows, int
 __device__ inline double2 load16(__amdgpu_buffer_rsrc_t r, int off) {
     return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 __device__ inline void store16(__amdgpu_buffer_rsrc_t r, int off, double2 v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, off, 0, 0);
@@ -63,44 +65,34 @@ __device__ inline void turn16(double2* v, Turn& X, int q, int kq) {
     wave_lds_fence();                    // before the next chunk's writes
 }
 
-// Accumulators of a tile: register r is row tile16_row of column lane%16.
 typedef float v4f __attribute__((ext_vector_type(4)));
-template <bool MIXED> struct Tile16Acc { typedef v4d type; };
-template <> struct Tile16Acc<true> { typedef v4f type; };
-template <bool MIXED>
-__device__ inline int tile16_row(int lane, int r) {
-    return MIXED ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
-}
 
-// sum_t alpha_t op(A_t) op(B_t) over the 16 x 16 tile at (i0, j0), by one wave;
-// MIXED: operands (after conjugation and alpha) rounded to FP32 and accumulated in
-// FP32.  The k range of every term
-// is taken 16 at a time, chunks w, w + KW, ... of each (KW waves share a tile); the
-// next chunk's loads (of the same or the next term) are issued before the current
-// chunk's MFMAs.  Entries of A and B past k are cleared; rows and columns outside the
+// sum_t alpha_t op(A_t) op(B_t) over the 16 x 16 tile at (i0, j0), by one wave:
+// register r is row lane/16 + 4 r of column lane%16.  The k range of every term is
+// taken 16 at a time; the next chunk's loads (of the same or the next term) are issued
+// before the current chunk's MFMAs.  Entries of A and B past k are cleared; rows and columns outside the
 // product only reach entries that are not stored.
-template <int KW, bool MIXED>
-__device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0, int w, int lane, Turn& XA, Turn& XB,
-                                  typename Tile16Acc<MIXED>::type& re, typename Tile16Acc<MIXED>::type& im) {
+__device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0, int lane, Turn& XA, Turn& XB, v4d& re,
+                                  v4d& im) {
     const int nt = o.head(offsetof(GemmOp, nterms) / 4);
     const int q = lane & 15, kq = lane >> 4;
-    re = im = typename Tile16Acc<MIXED>::type{};
+    re = im = v4d{};
     // The chunk to load next: term s at offset c0.  Element t of a lane lies along
     // k (row kq + 4 t of the tile, k = q) or across (row or column q, k = 4 t + kq):
-    // byte offsets va + t da (vb + t db), from one chunk to the wave's next ka (kb) more.
+    // byte offsets va + t da (vb + t db), from one chunk to the next ka (kb) more.
     int s = -1, c0 = 0, k = 0, va = 0, vb = 0, da = 0, db = 0, ka = 0, kb = 0;
     bool ah = false, bh = false;
     double2 alpha = make_double2(1.0, 0.0);
     __amdgpu_buffer_rsrc_t ra, rb;
     auto advance = [&]() {
-        c0 += 16 * KW;
+        c0 += 16;
         if (c0 < k) {
             va += ka;
             vb += kb;
             return;
         }
-        c0 = 16 * w;
-        do ++s; while (s < nt && o.term(s, offsetof(GemmTerm, k) / 4) <= c0);
+        c0 = 0;
+        do ++s; while (s < nt && o.term(s, offsetof(GemmTerm, k) / 4) <= 0);
         if (s >= nt) return;
         k = o.term(s, offsetof(GemmTerm, k) / 4);
         const int lda = o.term(s, offsetof(GemmTerm, lda) / 4), ldb = o.term(s, offsetof(GemmTerm, ldb) / 4);
@@ -119,10 +111,8 @@ __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0,
         vb = (lb + q + (bh ? j0 * ldb : j0)) * 16;
         da = 64 * lda;
         db = 64 * ldb;
-        ka = KW * (ah ? 256 * lda : 256);
-        kb = KW * (bh ? 256 : 256 * ldb);
-        va += w * (ah ? 256 * lda : 256);
-        vb += w * (bh ? 256 : 256 * ldb);
+        ka = ah ? 256 * lda : 256;
+        kb = bh ? 256 : 256 * ldb;
     };
     static_assert(offsetof(GemmTerm, A) == 0 && offsetof(GemmTerm, B) == 8, "pointers first");
     struct Chunk {
@@ -175,18 +165,10 @@ __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0,
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (4 * t >= c.left) break;                 // wave-uniform
-            if constexpr (MIXED) {
-                const float ax = (float)c.a[t].x, ay = (float)c.a[t].y, bx = (float)c.b[t].x, by = (float)c.b[t].y;
-                re = __builtin_amdgcn_mfma_f32_16x16x4f32(ax, bx, re, 0, 0, 0);
-                im = __builtin_amdgcn_mfma_f32_16x16x4f32(ax, by, im, 0, 0, 0);
-                re = __builtin_amdgcn_mfma_f32_16x16x4f32(-ay, by, re, 0, 0, 0);
-                im = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, bx, im, 0, 0, 0);
-            } else {
-                re = mfma64(c.a[t].x, c.b[t].x, re);
-                im = mfma64(c.a[t].x, c.b[t].y, im);
-                re = mfma64_nega(c.a[t].y, c.b[t].y, re);
-                im = mfma64(c.a[t].y, c.b[t].x, im);
-            }
+            re = mfma64(c.a[t].x, c.b[t].x, re);
+            im = mfma64(c.a[t].x, c.b[t].y, im);
+            re = mfma64_nega(c.a[t].y, c.b[t].y, re);
+            im = mfma64(c.a[t].y, c.b[t].x, im);
         }
     };
     advance();
