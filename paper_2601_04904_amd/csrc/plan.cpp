@@ -1740,15 +1740,28 @@ std::vector<uint64_t> make_key(Mode mode, bool fp64_rerun, const std::vector<int
     return k;
 }
 
+// Tile order entries that the products can take in any launches and tile shapes: the
+// tuning table may change after a handle's memory is sized, and a selected solve or
+// a factor launches fewer products together, which may then take smaller tiles.  An
+// order is padded to 8 queues of one length, by at most 7 entries for every product.
+size_t order_room(const Program& pg) {
+    size_t n = 0;
+    for (const GemmOp& g : pg.gemm) {
+        const int small = gemm_tiles_shape(g.m, g.n, kSmallShape);
+        n += (small_fits(g) && small <= 256 * kSmallRounds ? small : gemm_tiles_shape(g.m, g.n, 0)) + kNumXcd - 1;
+    }
+    return n;
+}
+
 // Device bytes of a compiled program's operation lists (each array starting
 // on a 256-byte boundary, as prepare_and_run lays them out).
 struct ProgLayout {
     size_t off_order, off_inv, off_add, off_norm, off_frec, off_fstep, off_ftask, total;
 };
-ProgLayout program_layout(const Program& pg) {
+ProgLayout program_layout(const Program& pg, size_t order_entries) {
     ProgLayout L;
     L.off_order = align256(pg.gemm.size() * sizeof(GemmOp));
-    L.off_inv = align256(L.off_order + pg.order.size() * sizeof(TileEntry));
+    L.off_inv = align256(L.off_order + order_entries * sizeof(TileEntry));
     L.off_add = align256(L.off_inv + pg.inv.size() * sizeof(InvJob));
     L.off_norm = align256(L.off_add + pg.add.size() * sizeof(AddOp));
     L.off_frec = align256(L.off_norm + pg.norm.size() * sizeof(NormJob));
@@ -1758,7 +1771,8 @@ ProgLayout program_layout(const Program& pg) {
     return L;
 }
 
-size_t program_bytes(const Program& pg) { return program_layout(pg).total; }
+// Room for it whatever tile shapes its products take.
+size_t program_bytes(const Program& pg) { return program_layout(pg, order_room(pg)).total; }
 
 // Layout of a handle's device block (see bt_si_sq_plan): workspace, inverse
 // scratch, status word, then room for kArenaPrograms operation lists the size
@@ -1817,7 +1831,7 @@ bt_status prepare_and_run(bt_si_sq_plan* h, Mode mode, const std::vector<int>& s
         if (pg.inv_scratch_bytes > h->inv_bytes)
             return set_err(h, BT_ERR_INVALID, "internal: inverse scratch too small");
         pg.flops = bt.flops;
-        const ProgLayout PL = program_layout(pg);
+        const ProgLayout PL = program_layout(pg, pg.order.size());
         const size_t total = PL.total;
         // Device room for the lists: the handle's arena, taken in order; when
         // it is full every cached program is dropped (after its streams are

@@ -31,3 +31,19 @@ def test_every_tile_of_a_launch_once(count, last):
     first = np.concatenate([[0], np.cumsum(tiles)[:-1]])
     assert np.array_equal(p[at], np.repeat(np.arange(count), tiles))
     assert np.array_equal(t[at], np.arange(len(p)) - first[p[at]])
+
+
+@pytest.mark.parametrize("specs", [[dict(n=64, b=512, a=0, partitions=8)], [dict(n=16, b=32, a=0, partitions=4)],
+                                   [dict(n=9, b=100, a=37, partitions=2), dict(n=7, b=300, a=300)] * 3])
+def test_handle_size_does_not_depend_on_the_tuning_table(specs):
+    """Memory sized under one table holds a handle created under another."""
+    from paper_2601_04904_amd import solver as S
+    saved = S.tune_table()
+    try:
+        sizes = []
+        for v in range(-1, _lib.BT_TILE_SHAPES):
+            S.set_tune_table([v] * _lib.BT_TUNE_ENTRIES)
+            sizes.append(S.batch_workspace_bytes(specs))
+        assert len(set(sizes)) == 1, sizes
+    finally:
+        S.set_tune_table(saved)
