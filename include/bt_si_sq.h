@@ -327,11 +327,12 @@ bt_status bt_si_sq_profile_stats(bt_si_sq_handle h, bt_kernel_stat* out, int32_t
  * precision (0 FP64, 1 mixed), size class (log2 of its largest output
  * dimension, 32..1024 -> 0..5) and work class (log2 of its 64 x 32 tile
  * count, 1..8192 -> 0..13); the shape of a class comes from a process-wide
- * tuning table, or from a default rule for classes never tuned.  Small
- * launches take 16 x 16 tiles whatever the table says (faster than each of
- * the three there; the shape is not one of the table's).  Handles
- * compile their launch lists when a pointer set is first used, so a table
- * change reaches launch lists compiled after it. */
+ * tuning table, or from a default rule for classes without an entry.  The
+ * rule has one more shape, 16 x 16 for small launches, which the table
+ * cannot name.  The shape does not change results.  Handles compile their
+ * launch lists when a pointer set is first used, so a table change reaches
+ * launch lists compiled after it; the size of a handle does not depend on
+ * the table. */
 #define BT_TILE_SHAPES 3
 #define BT_TUNE_SIZE_CLASSES 6
 #define BT_TUNE_WORK_CLASSES 14
@@ -339,7 +340,8 @@ bt_status bt_si_sq_profile_stats(bt_si_sq_handle h, bt_kernel_stat* out, int32_t
 
 /* Times every tile shape on synthetic grouped launches of square products
  * (sizes 64..1024, 1 to 4096 products per launch) in both precisions and
- * stores the fastest shape of each class reached into the tuning table.
+ * stores the fastest shape of each class reached into the tuning table, or
+ * -1 where the default rule's is as fast (within 3%).
  * Allocates and frees its own device scratch (about 300 MB), runs on
  * hip_stream (NULL: the null stream) and returns when done (a few seconds).
  * If report is not NULL, a text line per class ("prec size_class work_class

@@ -67,6 +67,11 @@ size_t bt_si_sq_diag_schedule(const bt_desc* desc, char* out, size_t cap);
 size_t bt_si_sq_diag_tile_order(int32_t count, const int32_t* tiles, const int32_t* k, uint64_t* out,
                                 size_t cap);
 
+/* Tile shape of a launch of count products m x n x k: 0..BT_TILE_SHAPES-1, or
+ * BT_TILE_SHAPES for the 16 x 16 tiles that the default rule gives small launches.  -1 for
+ * bad arguments.  Pure host computation. */
+int32_t bt_si_sq_diag_launch_shape(int32_t m, int32_t n, int32_t k, int32_t count, int32_t mixed);
+
 #ifdef __cplusplus
 }
 #endif

@@ -25,8 +25,8 @@
 // other, the two halves of the reduced system, SQ backward beside SI
 // backward - therefore share launches.  The A-chain runs on a second stream;
 // launch lists are compiled once per pointer set (optionally captured as a
-// HIP graph), and product tile shapes come from the tuning table or, for small
-// launches and classes never tuned, from a rule.
+// HIP graph), and product tile shapes come from the tuning table or, for classes
+// without an entry, from a rule.
 #include "../../include/bt_si_sq.h"
 #include "common.h"
 
@@ -957,8 +957,7 @@ GemmOp make_gemm_op(const OpRec& o) {
 // size class of its largest output (log2 of max(m, n), 5..10) and the class of
 // its work (log2 of its 64 x 32 tile count, 0..13); the shape comes from the
 // tuning table (filled by bt_si_sq_autotune or loaded with
-// bt_si_sq_tune_table) or, for small launches and classes never tuned, from the
-// default rule.
+// bt_si_sq_tune_table) or, for classes without an entry, from the default rule.
 constexpr int kMClasses = 6, kTClasses = 14;
 std::atomic<int> g_tune[2][kMClasses][kTClasses];
 std::once_flag g_tune_once;
@@ -1036,16 +1035,13 @@ void count_tiles(const GemmOp* ops, int n, long* tiles) {
     if (!fits) tiles[kSmallShape] = -1;
 }
 
-// The table holds the fastest of the three larger shapes; where the rule takes
-// kSmallShape, it is faster than each of them.
+// The shape of a launch: the table's if its class has one, else the rule's.
 int pick_shape(int mixed, int maxdim, const long* tiles) {
-    const int rule = default_shape(mixed, tiles);
-    if (rule == kSmallShape) return rule;
     tune_init();
     const int mc = log2_class(maxdim, 5, 5 + kMClasses - 1);
     const int tc = log2_class(std::max(1L, tiles[1]), 0, kTClasses - 1);
     const int v = g_tune[mixed ? 1 : 0][mc][tc].load();
-    return (v >= 0 && v < kGemmShapes) ? v : rule;
+    return (v >= 0 && v < kGemmShapes) ? v : default_shape(mixed, tiles);
 }
 
 // Order in which the workgroups of a product launch take its tiles.  Workgroups go
@@ -2412,8 +2408,9 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     const double2* A = reinterpret_cast<const double2*>(buf);
     const double2* B = reinterpret_cast<const double2*>(buf + in_bytes);
     double2* out = reinterpret_cast<double2*>(buf + 2 * in_bytes);
-    int found[2][kMClasses][kTClasses];
-    for (auto& a : found) for (auto& b : a) for (auto& c : b) c = -1;
+    constexpr int kNotReached = -2;
+    int found[2][kMClasses][kTClasses];          // a shape, or -1: the rule
+    for (auto& a : found) for (auto& b : a) for (auto& c : b) c = kNotReached;
     std::string rep;
     std::vector<GemmOp> ops;
     std::vector<TileEntry> order;
@@ -2443,8 +2440,11 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
                 }
                 float best_ms = 0.0f;
                 int best = -1;
-                float ms[kGemmShapes] = {0, 0, 0};
-                for (int sh = 0; sh < kGemmShapes && e == hipSuccess; ++sh) {
+                float ms[kGemmShapes + 1] = {0, 0, 0, 0};
+                long tiles[kGemmShapes + 1];
+                count_tiles(ops.data(), (int)nops, tiles);
+                const int rule = default_shape(prec, tiles);
+                for (int sh = 0; sh <= std::max(rule, kGemmShapes - 1) && e == hipSuccess; ++sh) {
                     for (auto& g : ops) g.tiles_n = gemm_tiles_n_shape(m, sh);
                     order.clear();
                     gemm_tile_order(ops.data(), (int)nops, sh, order);
@@ -2462,13 +2462,19 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
                     if (e == hipSuccess) e = hipEventSynchronize(ev1);
                     if (e == hipSuccess) e = hipEventElapsedTime(&ms[sh], ev0, ev1);
                     ms[sh] /= kReps;
-                    if (e == hipSuccess && (best < 0 || ms[sh] < best_ms)) { best = sh; best_ms = ms[sh]; }
+                    if (e == hipSuccess && sh < kGemmShapes && (best < 0 || ms[sh] < best_ms)) { best = sh; best_ms = ms[sh]; }
                 }
                 if (e != hipSuccess || best < 0) break;
-                // shapes within 3% of the fastest count as ties, broken toward the
-                // larger tile (fewer tiles and launches; keeps repeated tunings stable)
-                for (int sh = kGemmShapes - 1; sh >= 0; --sh)
-                    if (ms[sh] <= 1.03f * best_ms) { best = sh; break; }
+                // Shapes within 3% of the fastest count as ties.  No entry where the rule's is
+                // one: the rule knows the launch's own tiles, the entry holds for every
+                // launch of a class.  Else the larger tile (fewer tiles; keeps repeated tunings
+                // stable).
+                if (ms[rule] <= 1.03f * best_ms) {
+                    best = -1;
+                } else {
+                    for (int sh = kGemmShapes - 1; sh >= 0; --sh)
+                        if (ms[sh] <= 1.03f * best_ms) { best = sh; break; }
+                }
                 found[prec][mc][tc] = best;
                 char line[160];
                 snprintf(line, sizeof line, "%d %d %d %d %.1f %.1f %.1f\n", prec, mc, tc, best,
@@ -2487,7 +2493,7 @@ bt_status bt_si_sq_autotune(void* hip_stream, char* report, size_t cap) {
     for (int p = 0; p < 2; ++p)
         for (int mc = 0; mc < kMClasses; ++mc)
             for (int tc = 0; tc < kTClasses; ++tc)
-                if (found[p][mc][tc] >= 0) g_tune[p][mc][tc].store(found[p][mc][tc]);
+                if (found[p][mc][tc] != kNotReached) g_tune[p][mc][tc].store(found[p][mc][tc]);
     if (report && cap > 0) {
         const size_t nbytes = std::min(cap - 1, rep.size());
         memcpy(report, rep.data(), nbytes);
@@ -2662,4 +2668,19 @@ extern "C" size_t bt_si_sq_diag_tile_order(int32_t count, const int32_t* tiles, 
     tile_order(items, order);
     if (out) std::copy(order.begin(), order.begin() + std::min(cap, order.size()), out);
     return order.size();
+}
+
+extern "C" int32_t bt_si_sq_diag_launch_shape(int32_t m, int32_t n, int32_t k, int32_t count, int32_t mixed) {
+    if (m < 1 || n < 1 || k < 0 || count < 1) return -1;
+    GemmOp g;
+    memset(&g, 0, sizeof g);
+    g.m = m;
+    g.n = g.ldd = n;
+    g.nterms = 1;
+    g.t[0].k = k;
+    g.t[0].lda = g.t[0].ldb = 1;
+    long tiles[kGemmShapes + 1];
+    count_tiles(&g, 1, tiles);
+    for (long& t : tiles) t = t < 0 ? t : t * count;
+    return pick_shape(mixed, std::max(m, n), tiles);
 }

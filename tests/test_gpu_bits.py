@@ -66,3 +66,35 @@ def test_instance_alone_and_among_many(torch, specs, precision):
         for name in FIELDS:
             assert torch.equal(getattr(r[0], name), getattr(R[i], name)), (i, name)
             assert torch.equal(getattr(l[0], name), getattr(L[i], name)), (i, name)
+
+
+@pytest.mark.parametrize("n,b,a,P", [(12, 96, 40, 2), (17, 201, 33, 4)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solves_under_every_table(torch, n, b, a, P, precision):
+    """A solve with every launch in one shape of the table has the bits of the untuned one,
+    and is the oracle's."""
+    import oracle
+    from paper_2601_04904_amd import solver as S
+    from tests._util import rel_err
+    A, B = gen_problem(n, b, a, 0.3, 0.05, 5)
+    dA, dB = S.DeviceBlocks.from_host(A), S.DeviceBlocks.from_host(B)
+    saved = S.tune_table()
+    out = []
+    try:
+        for v in (-1, 0, 1, 2):
+            S.set_tune_table([v] * len(saved))
+            XR, XL = S.DeviceBlocks.empty(n, b, a), S.DeviceBlocks.empty(n, b, a)
+            sol = S.Solver(n, b, a, partitions=P,
+                           **(dict(precision=S.BT_MIXED, tol=1.0) if precision == "mixed" else {}))
+            sol.solve(dA, dB, XR, XL)
+            sol.sync()
+            sol.destroy()
+            out.append((XR, XL))
+    finally:
+        S.set_tune_table(saved)
+    for x in out[1:]:
+        for i in (0, 1):
+            for name in FIELDS:
+                assert torch.equal(getattr(x[i], name), getattr(out[0][i], name)), (i, name)
+    for x, ref in zip(out[0], oracle.solve_dense(A, B)):
+        assert rel_err(x.to_host(), ref) < (1e-4 if precision == "mixed" else 1e-11)

@@ -47,3 +47,21 @@ def test_handle_size_does_not_depend_on_the_tuning_table(specs):
         assert len(set(sizes)) == 1, sizes
     finally:
         S.set_tune_table(saved)
+
+
+@pytest.mark.parametrize("m,n,k,count", [(32, 32, 32, 1), (128, 128, 128, 3), (100, 37, 100, 2), (512, 512, 512, 32)])
+@pytest.mark.parametrize("mixed", [0, 1])
+def test_a_table_entry_is_taken(m, n, k, count, mixed):
+    """Every launch takes the shape that its class has in the table, small launches too;
+    without an entry small launches take the 16 x 16 tiles."""
+    from paper_2601_04904_amd import solver as S
+    shape = _lib.lib().bt_si_sq_diag_launch_shape
+    saved = S.tune_table()
+    try:
+        for v in range(_lib.BT_TILE_SHAPES):
+            S.set_tune_table([v] * _lib.BT_TUNE_ENTRIES)
+            assert shape(m, n, k, count, mixed) == v
+        S.set_tune_table([-1] * _lib.BT_TUNE_ENTRIES)
+        assert (shape(m, n, k, count, mixed) == _lib.BT_TILE_SHAPES) == (count < 32)
+    finally:
+        S.set_tune_table(saved)
