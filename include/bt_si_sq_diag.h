@@ -72,6 +72,10 @@ size_t bt_si_sq_diag_tile_order(int32_t count, const int32_t* tiles, const int32
  * bad arguments.  Pure host computation. */
 int32_t bt_si_sq_diag_launch_shape(int32_t m, int32_t n, int32_t k, int32_t count, int32_t mixed);
 
+/* Launches that the inverses of count blocks of sizes d (host array) take in one
+ * dependency level.  -1 for bad arguments.  Pure host computation. */
+int32_t bt_si_sq_diag_inverse_launches(int32_t count, const int32_t* d);
+
 #ifdef __cplusplus
 }
 #endif

@@ -30,6 +30,7 @@ EXPORTED = [
     "bt_si_sq_diag_gemm", "bt_si_sq_diag_inverse", "bt_si_sq_diag_schedule",
     "bt_si_sq_diag_inverse_noalloc", "bt_si_sq_diag_inverse_noalloc_max_bytes",
     "bt_si_sq_diag_tile_order", "bt_si_sq_diag_launch_shape",
+    "bt_si_sq_diag_inverse_launches",
 ]
 
 KERNEL_NAMES = {0: "product_fp64", 1: "product_mixed", 2: "inv_panel", 3: "inv_init",
@@ -153,6 +154,8 @@ def lib():
     L.bt_si_sq_diag_tile_order.restype = C.c_size_t
     L.bt_si_sq_diag_launch_shape.argtypes = [C.c_int32] * 5
     L.bt_si_sq_diag_launch_shape.restype = C.c_int32
+    L.bt_si_sq_diag_inverse_launches.argtypes = [C.c_int32, C.POINTER(C.c_int32)]
+    L.bt_si_sq_diag_inverse_launches.restype = C.c_int32
     _lib = L
     return L
 

@@ -72,6 +72,7 @@ struct InvJob {
 constexpr int kInvNB = 16;          // panel width (panel rows live in registers)
 constexpr int kInvMaxDim = 1024;    // 512 threads x 2 rows at most
 constexpr int kInvVariants = 6;     // kernel shapes (inv_variant)
+constexpr int kFirstPanelVariant = 2;   // from here on a launch per panel, below one launch
 
 // Scratch of one inverse job: W (d x d), perm and used (d each), each piece
 // starting on a 256-byte boundary.  inv_scratch_bytes is the span of one job's

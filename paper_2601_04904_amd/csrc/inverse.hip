@@ -360,7 +360,7 @@ void inv_small(const InvJob* __restrict__ jobs, DevStatus* status) {
 int inv_variant(int d) { return d <= 64 ? 0 : d <= 112 ? 1 : d <= 128 ? 2 : d <= 256 ? 3 : d <= 512 ? 4 : 5; }
 
 // Launches of one inverse of dimension d: panel steps p = 0 .. inv_steps(d) - 1.
-int inv_steps(int d) { return inv_variant(d) < 2 ? 1 : (d + kInvNB - 1) / kInvNB + 1; }
+int inv_steps(int d) { return inv_variant(d) < kFirstPanelVariant ? 1 : (d + kInvNB - 1) / kInvNB + 1; }
 
 template <int NW, int Q>
 static void launch_step(const InvJob* d_jobs, int njobs, int wg, int panel, DevStatus* status, hipStream_t s) {

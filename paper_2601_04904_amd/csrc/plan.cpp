@@ -1208,6 +1208,37 @@ bool compile_fused(Program& pg, const std::vector<OpRec>& ops) {
     return true;
 }
 
+// Kernel shape in which the blocks of each kernel shape (inv_variant) of one level are
+// inverted, given their number and their workgroups (one for the panel, one per column
+// block).  Blocks inverted panel by panel go along with the largest ones while they are
+// few: a launch lasts as long as its longest panel chain, and theirs are shorter.  But
+// the larger shape spends the larger block's rows on them, so with many the launches
+// of their own are cheaper.  Measured, us apart and together: 1 of 256 beside 1 of 512
+// 1129 and 843, 16 1212 and 1047, 32 1325 and 1320, 64 1520 and 1812, 256 2708 and 4984;
+// 16 of 256 beside 1 of 1024 3231 and 3299, 256 4853 and 11073; 32 of 512 beside 1 of 600
+// 4228 and 3836, 64 5781 and 6230.  Blocks up to 128 beside blocks up to 256: always
+// better (256 of 128: 650 and 589).  A row's arithmetic is the same in every shape.
+void share_panels(const int* count, const long* wgs, int* shape) {
+    constexpr long kFew = 288, kFew512 = 1056;
+    int top = 0;
+    for (int v = 0; v < kInvVariants; ++v) {
+        shape[v] = v;
+        if (count[v] > 0) top = v;
+    }
+    long moved = 0;
+    for (int v = top - 1; v >= kFirstPanelVariant; --v) {
+        if (count[v] == 0) continue;
+        const bool large = v >= 4;                  // one workgroup a CU in both shapes
+        const long w = wgs[v] + (large ? 0 : moved);
+        if (top == 3 || w <= (large ? kFew512 : kFew)) {
+            shape[v] = top;
+            if (!large) moved = w;
+        } else if (v == 2 && count[3] > 0 && shape[3] == 3) {
+            shape[v] = 3;
+        }
+    }
+}
+
 // Turn levelled operations into typed device arrays and a launch list.
 // Launches are ordered by level and, within a level, critical stream first;
 // the fused launch (BT_FUSED instances) comes first, on the main stream.
@@ -1235,12 +1266,21 @@ Program compile(std::vector<OpRec>& ops, int nlevels, char* inv_pool) {
             for (int i : bylevel[L])
                 if (ops[i].kind == K_INV && ops[i].cls == cls) { invs.push_back(i); wait = std::max(wait, ops[i].wait_other); }
             if (!invs.empty()) {
+                int count[kInvVariants] = {}, shape[kInvVariants];
+                long wgs[kInvVariants] = {};
+                for (int i : invs) {
+                    const int d = ops[i].D.r, v = inv_variant(d);
+                    ++count[v];
+                    wgs[v] += 1 + (d + kInvNB - 1) / kInvNB;
+                }
+                share_panels(count, wgs, shape);
                 std::stable_sort(invs.begin(), invs.end(), [&](int x, int y) {
-                    return inv_variant(ops[x].D.r) < inv_variant(ops[y].D.r);
+                    return shape[inv_variant(ops[x].D.r)] < shape[inv_variant(ops[y].D.r)];
                 });
                 size_t poff = 0;
                 const size_t first = pg.inv.size();
                 int maxd = 0;
+                int vcount[kInvVariants] = {}, vmaxd[kInvVariants] = {};
                 for (int i : invs) {
                     const OpRec& o = ops[i];
                     const int d = o.D.r;
@@ -1253,19 +1293,11 @@ Program compile(std::vector<OpRec>& ops, int nlevels, char* inv_pool) {
                     j.tag = o.tag;
                     poff = inv_bind_scratch(j, inv_pool, poff, d);
                     pg.inv.push_back(j);
+                    const int v = shape[inv_variant(d)];
+                    ++vcount[v];
+                    vmaxd[v] = std::max(vmaxd[v], d);
                 }
                 pg.inv_scratch_bytes = std::max(pg.inv_scratch_bytes, poff + 256);
-                // The blocks that are inverted panel by panel all take the kernel shape of
-                // the level's largest: a launch lasts as long as its longest panel
-                // chain, so the smaller blocks' launches come for free (blocks of up to 256
-                // and of up to 512 in one level: 17 launches of 17 us saved beside 25 us
-                // each), and a row's arithmetic is the same in every shape.
-                int vcount[kInvVariants] = {}, vmaxd[kInvVariants] = {};
-                for (int i : invs) {
-                    const int v = inv_steps(ops[i].D.r) > 1 ? inv_variant(maxd) : inv_variant(ops[i].D.r);
-                    ++vcount[v];
-                    vmaxd[v] = std::max(vmaxd[v], ops[i].D.r);
-                }
                 // per kernel shape: one launch for small blocks, else one per panel
                 // plus the one that applies the last panel and writes the results;
                 // the first carries the wait on the other stream
@@ -2683,4 +2715,19 @@ extern "C" int32_t bt_si_sq_diag_launch_shape(int32_t m, int32_t n, int32_t k, i
     count_tiles(&g, 1, tiles);
     for (long& t : tiles) t = t < 0 ? t : t * count;
     return pick_shape(mixed, std::max(m, n), tiles);
+}
+
+extern "C" int32_t bt_si_sq_diag_inverse_launches(int32_t count, const int32_t* d) {
+    if (count < 1 || !d) return -1;
+    std::vector<OpRec> ops(count);
+    char* base = reinterpret_cast<char*>((uintptr_t)1 << 40);
+    for (int i = 0; i < count; ++i) {
+        if (d[i] < 1 || d[i] > kInvMaxDim) return -1;
+        ops[i].kind = K_INV;
+        double2* p = reinterpret_cast<double2*>(base + (size_t)i * 2 * kInvMaxDim * kInvMaxDim * sizeof(double2));
+        ops[i].C = MatRef{p, d[i], d[i]};
+        ops[i].D = MatRef{p + (size_t)kInvMaxDim * kInvMaxDim, d[i], d[i]};
+    }
+    const int nl = levelize(ops);
+    return (int32_t)compile(ops, nl, base).launches.size();
 }

@@ -42,7 +42,9 @@ def test_product_bits_in_every_shape(torch, m, n, k, mixed):
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("specs", [[(6, 128, 0, 1)] * 16, [(5, 64, 37, 1)] * 24,
-                                   [(9, 100, 20, 2), (6, 200, 64, 1), (7, 48, 0, 3), (4, 256, 0, 1)] * 5])
+                                   [(9, 100, 20, 2), (6, 200, 64, 1), (7, 48, 0, 3), (4, 256, 0, 1)] * 5,
+                                   # inverses: 40 of 120 apart, 300 in the shape of 520
+                                   [(2, 300, 0, 1), (2, 520, 0, 1)] + [(2, 120, 0, 1)] * 40])
 def test_instance_alone_and_among_many(torch, specs, precision):
     from paper_2601_04904_amd import solver as S
     kw = dict(precision=S.BT_MIXED, tol=1.0) if precision == "mixed" else {}

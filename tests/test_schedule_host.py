@@ -65,3 +65,29 @@ def test_a_table_entry_is_taken(m, n, k, count, mixed):
         assert (shape(m, n, k, count, mixed) == _lib.BT_TILE_SHAPES) == (count < 32)
     finally:
         S.set_tune_table(saved)
+
+
+def panels(d):
+    """Launches of blocks of d alone: a panel of 16 columns each, and one to write the result."""
+    return 1 if d <= 112 else -(-d // 16) + 1
+
+
+@pytest.mark.parametrize("sizes,together", [
+    ([(256, 1), (512, 1)], True), ([(256, 16), (512, 1)], True), ([(256, 64), (512, 1)], False),
+    ([(256, 64), (1024, 1)], False), ([(128, 32), (600, 1)], True), ([(128, 64), (600, 1)], False),
+    ([(512, 32), (600, 1)], True), ([(512, 64), (600, 1)], False), ([(128, 256), (256, 1)], True),
+    ([(120, 1), (200, 1), (300, 1)], True)])
+def test_panel_launches_are_shared_by_few_blocks_only(sizes, together):
+    d = np.repeat([s for s, _ in sizes], [c for _, c in sizes]).astype(np.int32)
+    got = _lib.lib().bt_si_sq_diag_inverse_launches(len(d), d.ctypes.data_as(C.POINTER(C.c_int32)))
+    assert got == (panels(max(d)) if together else sum(panels(s) for s, _ in sizes))
+
+
+def test_panel_launches_next_to_small_blocks_and_of_three_shapes():
+    def count(sizes):
+        d = np.repeat([s for s, _ in sizes], [c for _, c in sizes]).astype(np.int32)
+        return _lib.lib().bt_si_sq_diag_inverse_launches(len(d), d.ctypes.data_as(C.POINTER(C.c_int32)))
+    assert count([(40, 3), (100, 2), (257, 1)]) == 2 + panels(257)
+    # the blocks of 128 go with those of 256 where these stay apart from the largest
+    assert count([(128, 200), (256, 100), (1024, 1)]) == panels(256) + panels(1024)
+    assert count([(128, 200), (256, 1), (1024, 1)]) == panels(128) + panels(1024)
