@@ -18,13 +18,14 @@ struct GemmTerm {
 
 constexpr int kMaxTerms = 6;
 constexpr int kGemmShapes = 3;     // product tile shapes: 32x32, 64x32, 64x64 complex
-constexpr int kSmallShape = 3;     // 16x16, chosen by rule for small launches only
+constexpr int kSmallShape = 3;     // 16x16, for small launches, chosen by the default rule only
 constexpr int kTermAH = 1;
 constexpr int kTermBH = 2;
 
 // D = beta * C + sum_t alpha_t op(A_t) op(B_t), D and C m x n (C may alias D
 // or be null, then beta is ignored).  Products of one launch are independent of
-// each other.
+// each other.  Every tile shape sums an entry in one order, from beta C on (in complex64
+// to it), k upwards, term by term, so the bits do not depend on the launch.
 struct GemmOp {
     double2* D;
     const double2* C;

@@ -119,7 +119,8 @@ __device__ void fused_add(const AddOp& op, int tid) {
 // and handed over through LDS, and the step after that is read meanwhile, so no
 // step waits for its own description.
 // FW waves per workgroup: 8 while every instance has a CU to itself, else 4 (one
-// instance 1.12 against 1.30 ms; 512 of them 3.3 against 3.0).
+// instance 1.12 against 1.30 ms; 512 of them 3.3 against 3.0).  With 4, 48 bytes a lane go
+// to scratch, beside scalars kept in vector registers in both.
 template <int FW>
 __global__ __launch_bounds__(64 * FW)
 void fused_solve(const FusedTask* __restrict__ tasks, const FusedStep* __restrict__ steps,

@@ -29,8 +29,8 @@
 //
 // What bounds it: the column chain of the panel workgroup, one CU while the others
 // wait.  Measured alone, us per inverse (FP64 FMAs with every column of the panel
-// updated at every pivot -> this form): d = 32 41 -> 20, 64 81 -> 45, 100 133 ->
-// 114, 128 162 -> 139, 256 377 -> 288, 512 974 -> 843, 1024 3030 -> 2830.
+// updated at every pivot -> this form): d = 32 41 -> 19, 64 81 -> 43, 100 133 ->
+// 112, 128 162 -> 138, 256 377 -> 289, 512 974 -> 843, 1024 3030 -> 2822.
 //
 // One launch per panel p = 0 .. np (np = ceil(d / NB)):
 //   p < np : the panel workgroup applies T_{p-1} to block p and eliminates it;
@@ -323,8 +323,9 @@ __device__ void step_panel(const InvJob& J, int p, int tid, DevStatus* status) {
 
 // grid.x = njobs * wg_per_job; workgroup 0 of a job is the panel workgroup.
 template <int NW, int Q>
-// At most 256 registers (two waves per SIMD): with 128 the column loop spills,
-// 30.6 against 26.9 us per launch at d = 512.
+// At most 256 registers (two waves per SIMD): with 128 the column loop of 8 x 64 rows
+// spills, 30.6 against 26.9 us per launch at d = 512.  At 256 only 8 x 128 rows spill, 12
+// registers (36 bytes of scratch a lane).
 __global__ __launch_bounds__(64 * NW, 2)
 void inv_step(const InvJob* __restrict__ jobs, int p, int wg_per_job, DevStatus* status) {
     const int job = blockIdx.x / wg_per_job;
@@ -355,8 +356,8 @@ void inv_small(const InvJob* __restrict__ jobs, DevStatus* status) {
 
 // Kernel shape for dimension d.  Up to 112 one workgroup inverts the block in one
 // launch (0, 1), above it is a launch per panel (2 .. 5).  Measured, us for one
-// inverse, one workgroup against panels: d = 64 44 / 69, 100 114 / 117, 112 127 /
-// 127, 128 158 / 144.
+// inverse, one workgroup against panels: d = 64 43 / 72, 100 112 / 114, 112 127 /
+// 123 (in nine launches), 128 157 / 138.
 int inv_variant(int d) { return d <= 64 ? 0 : d <= 112 ? 1 : d <= 128 ? 2 : d <= 256 ? 3 : d <= 512 ? 4 : 5; }
 
 // Launches of one inverse of dimension d: panel steps p = 0 .. inv_steps(d) - 1.

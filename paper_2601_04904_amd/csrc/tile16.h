@@ -70,8 +70,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // sum_t alpha_t op(A_t) op(B_t) over the 16 x 16 tile at (i0, j0), by one wave:
 // register r is row lane/16 + 4 r of column lane%16.  The k range of every term is
 // taken 16 at a time; the next chunk's loads (of the same or the next term) are issued
-// before the current chunk's MFMAs.  Entries of A and B past k are cleared; rows and columns outside the
-// product only reach entries that are not stored.
+// before the current chunk's MFMAs.  Entries of A and B past k are cleared; rows and
+// columns outside the product only reach entries that are not stored.
 __device__ inline void tile16_sum(const OpRegs& o, int m, int n, int i0, int j0, int lane, Turn& XA, Turn& XB, v4d& re,
                                   v4d& im) {
     const int nt = o.head(offsetof(GemmOp, nterms) / 4);

@@ -359,7 +359,8 @@ def set_tune_table(table):
 
 
 def autotune(stream=None, cache=None):
-    """Time the product tile shapes on this device and fill the tuning table.
+    """Time the product tile shapes on this device and fill the tuning table (-1, the default
+    rule, where its shape is as fast as the fastest).
 
     Returns the report lines ("prec size_class work_class shape us0 us1 us2").
     With cache (a file path) the table is loaded from it if present, else
@@ -385,7 +386,8 @@ def autotune(stream=None, cache=None):
 
 def diag_gemm(alpha, A, opA, B, opB, beta=0.0, Cin=None, D=None, mixed=False, stream=None, shape=-1):
     """D = beta Cin + alpha op(A) op(B) on the device (2-D complex128 tensors); returns D.
-    shape: product tile shape, -1 for the tuning table's choice."""
+    shape: product tile shape, -1 for the one such a launch takes in a solve (the tuning
+    table's, else the default rule's).  The shape does not change the result."""
     torch = _torch()
     m = A.shape[1] if opA else A.shape[0]
     k = A.shape[0] if opA else A.shape[1]

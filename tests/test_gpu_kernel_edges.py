@@ -1,9 +1,8 @@
 """The product and inverse kernels at the sizes where their shapes change.
 
 Products: k around the 16-deep stage, sizes around the tiles, every operand
-order with alpha = -1 and a general alpha (the accumulators change sign between
-terms of different sign; a general alpha is multiplied into an operand), and a
-launch with more products than one 64-lane search covers.  Inverses: dimensions
+order with alpha = -1 (a change of the accumulators' sign) and a general alpha
+(multiplied into an operand), and launches of more than 128 products.  Inverses: dimensions
 around each kernel shape, with rows that force pivoting.  Tolerances: a product
 of k terms in FP64 is within (k + 4) eps of sum |a||b|; an inverse with partial
 pivoting is held to 50 eps sqrt(d) cond, as the other inverse tests.
@@ -50,7 +49,7 @@ def test_product_stage_edges(torch, m, n, k, alpha):
 @pytest.mark.parametrize("m,n", [(1, 1), (16, 17), (15, 33), (1, 200), (144, 16), (129, 127)])
 def test_small_launch_tiles(torch, m, n, k):
     """The shape that the default rule takes for one small product: 16 x 16 tiles
-    whose k is split over the waves of a workgroup."""
+    shared by the waves of a workgroup."""
     from paper_2601_04904_amd.solver import diag_gemm
     rng = np.random.default_rng(m * 1000 + n * 50 + k)
     beta = 0.25 - 1.5j
