@@ -1051,9 +1051,9 @@ int pick_shape(int mixed, int maxdim, const long* tiles) {
 // longest products first.  So the XCDs have equal work even where a launch mixes
 // one-term and three-term products, the short tiles come last and fill the tail,
 // and neighbouring tiles (which share operand rows or columns) mostly still meet in
-// one L2: n=64 b=512 P=8 moves 212 MB of HBM per product launch, 1.63 times the operands
-// and results (191 MB with one contiguous run of all tiles per XCD, which left the XCDs
-// that got the long products working alone), and its products take 42.2 ms (46.2).
+// one L2.  Against one contiguous run of all tiles per XCD, which left the XCDs that got
+// the long products working alone, n=64 b=512 P=8 (in mostly 64 x 64 tiles) moves more HBM
+// per product launch, 212 MB for 191, and its products take 42.2 ms for 46.2.
 struct OrderItem {
     double k;      // of the product, summed over its terms
     int tiles;
